@@ -1834,11 +1834,15 @@ __global__ __launch_bounds__(kGemvThreads) void k_gateup(Dims D, LayerPtrs L, Ro
   tg.init(D.d, dyn);
   // ---- everything needed before the weights: issued first ----
   // (unconditional loads at clamped indices; consumed after the prime)
-  float sv[kBins];
-  {
-    const int q = min(tid, rm.M * PO - 1);
+  // (eight dual sequences of rank 16 have 528 sums, more than threads: NSV per thread)
+  constexpr int NSV = (MT * (1 + 2 * kMaxRank) + kGemvThreads - 1) / kGemvThreads;
+  float sv[NSV][kBins];
 #pragma unroll
-    for (int b = 0; b < kBins; ++b) sv[b] = bin_o_at(ws, D, layer, b, q / PO)[q % PO];
+  for (int k = 0; k < NSV; ++k) {
+    if (k > 0 && k * kGemvThreads >= rm.M * PO) break;   // (uniform)
+    const int q = min(tid + k * kGemvThreads, rm.M * PO - 1);
+#pragma unroll
+    for (int b = 0; b < kBins; ++b) sv[k][b] = bin_o_at(ws, D, layer, b, q / PO)[q % PO];
   }
   const float* rows[MT];
 #pragma unroll
@@ -1859,11 +1863,14 @@ __global__ __launch_bounds__(kGemvThreads) void k_gateup(Dims D, LayerPtrs L, Ro
   tg.prime(n_local, ptr);
   __builtin_amdgcn_sched_barrier(0);
   sk_rm_copy(rmu, rm);
-  if (tid < rm.M * PO) {
+#pragma unroll
+  for (int k = 0; k < NSV; ++k) {
+    const int q = tid + k * kGemvThreads;
+    if (q >= rm.M * PO) break;
     float a = 0.f;
 #pragma unroll
-    for (int b = 0; b < kBins; ++b) a += sv[b];
-    stat[tid] = a;
+    for (int b = 0; b < kBins; ++b) a += sv[k][b];
+    stat[q] = a;
   }
   if (pre_b && tid < 2 * 16 * D.r) {
     const int which = tid / (16 * D.r);

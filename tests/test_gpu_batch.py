@@ -1,0 +1,53 @@
+"""Batched decoding and chunks at the sizes where their kernels can go wrong
+(rows, ranks and context lengths at the edges of tiles and splits), against
+the oracle under the rule of ``gpu_harness``."""
+import numpy as np
+import pytest
+import torch
+
+import synth
+from tests.gpu_harness import Pair, Tally
+
+pytestmark = pytest.mark.gpu
+
+
+def batch_step(pair: Pair, lens, t: Tally, *, tol=None, seed=3):
+    """One dual step of sequences with random cache content of the given
+    lengths: logits, h, p, signal, token and the new cache entries."""
+    cfg, B, dev, tol = pair.cfg, len(lens), pair.dev, tol or pair.tol
+    N = cfg.n_layers
+    for s, n in enumerate(lens):
+        for l, (K, V) in synth.synthetic_kv(cfg, n, seq=s).items():
+            if n:
+                pair.kv.load(s, l, K, V)
+                pair.caches[s].load(l, K, V)
+    toks = synth.prompt_ids(cfg, B, seed=seed)
+    out = {k: torch.zeros(B * n, dtype=torch.float32, device=dev)
+           for k, n in (("signal", N), ("logits", cfg.vocab), ("h_out", cfg.d_model), ("p_out", cfg.d_model))}
+    nxt = torch.zeros(B, dtype=torch.int32, device=dev)
+    gates = list(range(1, N))
+    pair.model.decode_step(torch.tensor(toks, dtype=torch.int32, device=dev),
+                           torch.tensor(lens, dtype=torch.int32, device=dev), pair.kv.desc(), gates=gates, tau=0.9,
+                           mode="observe", next_token=nxt, **out)
+    torch.cuda.synchronize()
+    got = {k: v.cpu().numpy().reshape(B, -1) for k, v in out.items()}
+    for s, n in enumerate(lens):
+        r = pair.orc.decode_step(int(toks[s]), n, pair.caches[s], gates=gates, tau=0.9, mode="observe")
+        t.rel(got["logits"][s], r.logits, tol, f"seq {s} logits")
+        t.rel(got["h_out"][s], r.h, tol, f"seq {s} h")
+        t.rel(got["p_out"][s], r.p, tol, f"seq {s} p")
+        t.close(got["signal"][s], r.signal, tol, f"seq {s} signal")
+        t.token(int(nxt[s].item()), r.logits, tol, f"seq {s} token")
+        pair.check_cache(s, n, n + 1, t, f"seq {s}")
+        t.steps += 1
+
+
+@pytest.mark.parametrize("rank,B", [(16, 8), (32, 4), (32, 8)])
+def test_more_adapter_sums_than_threads(rank, B):
+    """Ranks at which the gate/up kernel's rows x (1 + 2 rank) adapter sums
+    outnumber its 512 threads (float32 weights: 1e-4)."""
+    cfg = synth.CONFIGS["tiny"].replace(name=f"tiny_r{rank}", rank=rank)
+    pair = Pair(cfg, synth.make_weights(cfg), max_ctx=64, max_batch=B, n_seqs=B, table_seed=7)
+    t = Tally()
+    batch_step(pair, [5, 19, 37, 2, 11, 30, 8, 23][:B], t)
+    assert t.steps == B and t.arrays >= 6 * B
