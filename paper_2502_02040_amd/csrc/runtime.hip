@@ -22,6 +22,7 @@
 #include "step_kernels.h"
 #include "sk_kernels.h"
 #include "sk_attn.h"
+#include "mf_attn.h"
 #include "rw_kernels.h"
 #include "arla.h"
 #include "persist.h"
@@ -401,6 +402,7 @@ struct m2r2_ctx {
   WS ws;
   // kernel timing (measurement only)
   Resident resident;
+  int cus = 0;   // compute units
   // stream-K GEMVs of the one- and two-row class
   bool sk_on = false;
   int sk_grid = 0;
@@ -719,6 +721,30 @@ m2r2_status run_layers_sk(m2r2_ctx* c, const RowMap& rm, const StepIO& io, const
   return M2R2_OK;
 }
 
+// Splits of the matrix-core attention (mf_attn.h) for `nseq` sequences, or 0
+// where it does not apply: a bfloat16 cache, one or two rows per sequence or
+// one sequence's chunk of slow rows.  Two workgroups are resident per compute
+// unit; about four per compute unit even out sequences of different lengths.
+int mf_splits(const m2r2_ctx* c, const RowMap& rm, const KVPtrs& kv, int rows_per_seq) {
+  if (!c->D.kvbf16 || is_flops(c->cfg)) return 0;
+  if (rows_per_seq > 2 && (rm.nseq > 1 || has_fast_row(rm))) return 0;
+  if ((long long)kv.num_blocks * c->D.H * kv.bs >= 1LL << 31) return 0;   // rows are numbered in 32 bits
+  const int want = std::max(1, 4 * c->cus / (rm.nseq * c->D.H));
+  const int fit = (c->max_ctx + kMfMinTokens - 1) / kMfMinTokens;          // splits of at least kMfMinTokens
+  const int need = (c->max_ctx + kMfMaxTokens - 1) / kMfMaxTokens;
+  const int S = std::max(need, std::min(want, fit));
+  return S <= 63 && S <= c->lay.S_max ? S : 0;
+}
+
+template <int WB, int HD>
+void mf_launch(const m2r2_ctx* c, const LayerPtrs& L, const RowMap& rm, const StepIO& io, const KVPtrs& kv, int l, int S,
+               int rows_per_seq, hipStream_t st) {
+  const dim3 grid(c->D.H, rm.nseq, S);
+  const size_t lds = mf_attn_lds_bytes(c->max_ctx, S);
+  if (rows_per_seq <= 2) km_attn<WB, HD, 2><<<grid, kMfThreads, lds, st>>>(c->D, L, rm, c->ws, io, kv, l, S);
+  else km_attn<WB, HD, 16><<<grid, kMfThreads, lds, st>>>(c->D, L, rm, c->ws, io, kv, l, S);
+}
+
 template <int WB, int KB, int HD, int MT>
 m2r2_status run_layers_t(m2r2_ctx* c, const RowMap& rm, const StepIO& io, const KVPtrs& kv, int n_layers_run,
                          hipStream_t st) {
@@ -746,12 +772,16 @@ m2r2_status run_layers_t(m2r2_ctx* c, const RowMap& rm, const StepIO& io, const 
   if (!short_attn && S + 1 > 64)
     return fail(M2R2_E_SHAPE, "context too long for the attention merge (max_ctx %d)", c->max_ctx);
   const size_t smem = attn_smem_bytes();
+  // M2R2_ATTN_CHUNKS asks for the short-chain attention
+  const int SM = c->attn_chunks ? 0 : mf_splits(c, rm, kv, rows_per_seq);
   const Grids G = grids<WB, MT>(c);
   HIP_TRY(arla_after<WB>(c, io, -1, st));   // the first interval's restart state
   for (int l = 0; l < n_layers_run; ++l) {
     const LayerPtrs& L = c->layers[l];
     TIMED(0, (k_qkv<WB, MT><<<G.qkv, kGemvThreads, G.l_d, st>>>(D, L, rm, c->ws, io, l)));
-    if (short_attn && S2 > 0 && NCA == 4)
+    if (SM > 0)
+      TIMED(1, (mf_launch<WB, HD>(c, L, rm, io, kv, l, SM, rows_per_seq, st)));
+    else if (short_attn && S2 > 0 && NCA == 4)
       TIMED(1, (ks_attn<WB, KB, HD, 4><<<dim3(S2, D.H, rm.nseq), kSkAttnThreads, sk_attn_lds_bytes(HD, D.r, WB),
                                           st>>>(D, L, rm, c->ws, io, kv, l, S2)));
     else if (short_attn && S2 > 0)
@@ -1622,6 +1652,7 @@ M2R2_API m2r2_status m2r2_create(const m2r2_config* cfg, const m2r2_weights* w, 
 
   hipError_t e = hipGetDevice(&c->device);
   // the no-allocation decode step's scratch: its address on this device
+  if (e == hipSuccess) e = hipDeviceGetAttribute(&c->cus, hipDeviceAttributeMultiprocessorCount, c->device);
   if (e == hipSuccess) e = scratch_setup(c->device);
   if (e == hipSuccess) e = hipMemset(workspace, 0, lay.total);
   if (e == hipSuccess) {

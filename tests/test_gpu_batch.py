@@ -51,3 +51,53 @@ def test_more_adapter_sums_than_threads(rank, B):
     t = Tally()
     batch_step(pair, [5, 19, 37, 2, 11, 30, 8, 23][:B], t)
     assert t.steps == B and t.arrays >= 6 * B
+
+
+# head_dim 64, 96 and 128 with a bfloat16 cache; float32 weights too
+MF_CONFIGS = {
+    "hd64": synth.CONFIGS["tiny"].replace(name="hd64", kvdtype="bf16"),
+    "hd96": synth.CONFIGS["small_bf16"],
+    "hd128": synth.CONFIGS["small_rw"],
+}
+
+
+@pytest.mark.parametrize("name", MF_CONFIGS)
+@pytest.mark.parametrize("block_size", [1, 16, 24])
+@pytest.mark.parametrize("lens", [(0, 1, 31, 32, 33), (127, 128, 129), (255, 257, 300, 511, 640, 2, 16, 1000)])
+def test_batch_attention_context_edges(name, block_size, lens):
+    """Contexts at the edges of the matrix-core attention's tiles (32 tokens),
+    waves and splits (128 tokens), pages of one, 16 and 24 tokens."""
+    cfg = MF_CONFIGS[name]
+    pair = Pair(cfg, synth.make_weights(cfg), max_ctx=max(lens) + 20, block_size=block_size, max_batch=len(lens),
+                n_seqs=len(lens), table_seed=11)
+    t = Tally()
+    # a cached value on the other side of a bfloat16 rounding is 2^-8 of itself
+    batch_step(pair, lens, t, tol=2e-2)
+    assert t.steps == len(lens)
+
+
+@pytest.mark.parametrize("name", MF_CONFIGS)
+@pytest.mark.parametrize("ctx,n", [(0, 3), (0, 16), (1, 15), (31, 7), (128, 9), (129, 16), (700, 5), (1000, 16)])
+def test_chunk_attention_context_edges(name, ctx, n):
+    """A chunk of n slow rows after ctx cached positions: targets and the
+    chunk's cache entries in every layer."""
+    cfg = MF_CONFIGS[name]
+    pair = Pair(cfg, synth.make_weights(cfg), max_ctx=ctx + 40, block_size=16, table_seed=13)
+    # float32 weights with a bfloat16 cache: a value whose rounding falls on
+    # the other side is one unit in the last place off, at most 2^-7 of itself
+    pair.tol = max(pair.tol, 2.0 ** -7)
+    t = Tally()
+    if ctx:
+        for l, (K, V) in synth.synthetic_kv(cfg, ctx).items():
+            pair.kv.load(0, l, K, V)
+            pair.caches[0].load(l, K, V)
+    toks = [int(x) for x in synth.prompt_ids(cfg, n, seed=9)]
+    dev = pair.dev
+    pos, targets = torch.tensor([ctx], dtype=torch.int32, device=dev), torch.zeros(16, dtype=torch.int32, device=dev)
+    pair.model.verify(torch.tensor(toks, dtype=torch.int32, device=dev), n, pos, pair.kv.desc(), targets)
+    torch.cuda.synchronize()
+    ref = pair.orc.slow_chunk(toks, ctx, pair.caches[0])
+    for i in range(n):
+        t.token(int(targets[i].item()), ref[i], pair.tol, f"row {i}")
+    pair.check_cache(0, ctx, ctx + n, t)
+    assert int(pos.item()) == ctx + n == int(pair.kv.seq_lens[0].item())
