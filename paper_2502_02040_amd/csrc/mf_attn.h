@@ -479,7 +479,7 @@ __global__ __launch_bounds__(kMfThreads, 2) void km_attn(Dims D, LayerPtrs L, Ro
     }
     if (s_eff == 1) {
       const float o = a / l;
-      ws.O[(size_t)(first + i) * qd + h * HD + d] = o;
+      put_o(D, rm, ws, first + i, h * HD + d, o);
       q_s[i][d] = o;
     } else {
       float* pp = part + ((size_t)sp * kMaxRows + i) * stride;
@@ -535,7 +535,7 @@ __global__ __launch_bounds__(kMfThreads, 2) void km_attn(Dims D, LayerPtrs L, Ro
 #pragma unroll 4
       for (int u = PF; u < s_eff; ++u) v += mw[i][u] * ld_agent(part + ((size_t)u * kMaxRows + i) * stride + 2 + d);
       v *= linv[i];
-      ws.O[(size_t)(first + i) * qd + h * HD + d] = v;
+      put_o(D, rm, ws, first + i, h * HD + d, v);
       q_s[i][d] = v;
     }
   }

@@ -23,6 +23,7 @@
 #include "sk_kernels.h"
 #include "sk_attn.h"
 #include "mf_attn.h"
+#include "tp_kernels.h"
 #include "rw_kernels.h"
 #include "arla.h"
 #include "persist.h"
@@ -38,8 +39,11 @@ using namespace m2r2;
 // never passes the array's name to a kernel (on the host it is only a
 // stand-in symbol): its device address is looked up once per device with
 // hipGetSymbolAddress and used instead.
+// A context's scratch besides its operand planes (at most 1 MiB each for X, O
+// and the SwiGLU activations) may take kNoAllocScratchBytes.
 constexpr size_t kNoAllocScratchBytes = (size_t)32 << 20;
-static __device__ __align__(256) unsigned char scratch[kNoAllocScratchBytes];
+constexpr size_t kNoAllocPlaneBytes = (size_t)3 << 20;
+static __device__ __align__(256) unsigned char scratch[kNoAllocScratchBytes + kNoAllocPlaneBytes];
 
 namespace {
 
@@ -109,6 +113,7 @@ struct Layout {
   size_t X, PIN, QKV, O, ACT, bin_d, bin_o, bin_gu, uo, att, att_cnt, lm_val, lm_idx, lm_cnt, exited, exitb,
       reinit, err, sig, arla_kv, arla_q, arla_sig, arla_cnt, rope, sk_part, sk_cnt, total;
   size_t fsc, fqkv, lrz;                 // FLOPs-optimised fast stream: slow scores, fast q/k/v, low-rank head
+  size_t XB, OB, AB, plane_bytes;        // operand planes of X, O, ACT (bf16 weights), and their total
   size_t scratch_begin, counters_begin, scratch_end;   // per-call scratch [begin, end), counters [counters_begin, end)
   size_t pk_sd, pk_so, pk_sgu, pk_bar, pk_rel, layers_d;   // one-launch step: statistics slots, barrier, layer table
   int pk_so_w, pk_sgu_w;
@@ -267,6 +272,13 @@ Layout make_layout(const m2r2_config& c, int max_batch, int max_chunk, int max_c
   L.fsc = take(flops ? sizeof(float) * (size_t)fh * max_ctx : 0);
   L.fqkv = take(flops ? sizeof(float) * (size_t)fh * 3 * c.head_dim : 0);
   L.lrz = take(sizeof(float) * std::max(c.head_rank, 1));
+  // activations in operand order (passes of 3 and more rows, bf16 weights)
+  const bool planes = wb && !moe;
+  const size_t planes0 = off;
+  L.XB = take(planes ? tp_plane_bytes(d) : 0);
+  L.OB = take(planes ? tp_plane_bytes(qdim) : 0);
+  L.AB = take(planes ? tp_plane_bytes(c.ffn) : 0);
+  L.plane_bytes = off - planes0;
   // arrival counters (zero between passes: the last arriver resets them)
   L.counters_begin = off;
   L.att_cnt = take(sizeof(uint32_t) * kMaxSeq * c.n_heads);
@@ -654,6 +666,30 @@ bool has_fast_row(const RowMap& rm) {
   return false;
 }
 
+// Splits of the matrix-core attention (mf_attn.h) for `nseq` sequences, or 0
+// where it does not apply: a bfloat16 cache, one or two rows per sequence or
+// one sequence's chunk of slow rows.  Two workgroups are resident per compute
+// unit; about four per compute unit even out sequences of different lengths.
+int mf_splits(const m2r2_ctx* c, const RowMap& rm, const KVPtrs& kv, int rows_per_seq) {
+  if (!c->D.kvbf16 || is_flops(c->cfg)) return 0;
+  if (rows_per_seq > 2 && (rm.nseq > 1 || has_fast_row(rm))) return 0;
+  if ((long long)kv.num_blocks * c->D.H * kv.bs >= 1LL << 31) return 0;   // rows are numbered in 32 bits
+  const int want = std::max(1, 4 * c->cus / (rm.nseq * c->D.H));
+  const int fit = (c->max_ctx + kMfMinTokens - 1) / kMfMinTokens;          // splits of at least kMfMinTokens
+  const int need = (c->max_ctx + kMfMaxTokens - 1) / kMfMaxTokens;
+  const int S = std::max(need, std::min(want, fit));
+  return S <= 63 && S <= c->lay.S_max ? S : 0;
+}
+
+template <int WB, int HD>
+void mf_launch(const m2r2_ctx* c, const LayerPtrs& L, const RowMap& rm, const StepIO& io, const KVPtrs& kv, int l, int S,
+               int rows_per_seq, hipStream_t st) {
+  const dim3 grid(c->D.H, rm.nseq, S);
+  const size_t lds = mf_attn_lds_bytes(c->max_ctx, S);
+  if (rows_per_seq <= 2) km_attn<WB, HD, 2><<<grid, kMfThreads, lds, st>>>(c->D, L, rm, c->ws, io, kv, l, S);
+  else km_attn<WB, HD, 16><<<grid, kMfThreads, lds, st>>>(c->D, L, rm, c->ws, io, kv, l, S);
+}
+
 // One or two rows: row-per-wave GEMVs and the short-chain attention.
 template <int WB, int KB, int HD>
 m2r2_status run_layers_rw(m2r2_ctx* c, const RowMap& rm, const StepIO& io, const KVPtrs& kv, int n_layers_run,
@@ -721,29 +757,43 @@ m2r2_status run_layers_sk(m2r2_ctx* c, const RowMap& rm, const StepIO& io, const
   return M2R2_OK;
 }
 
-// Splits of the matrix-core attention (mf_attn.h) for `nseq` sequences, or 0
-// where it does not apply: a bfloat16 cache, one or two rows per sequence or
-// one sequence's chunk of slow rows.  Two workgroups are resident per compute
-// unit; about four per compute unit even out sequences of different lengths.
-int mf_splits(const m2r2_ctx* c, const RowMap& rm, const KVPtrs& kv, int rows_per_seq) {
-  if (!c->D.kvbf16 || is_flops(c->cfg)) return 0;
-  if (rows_per_seq > 2 && (rm.nseq > 1 || has_fast_row(rm))) return 0;
-  if ((long long)kv.num_blocks * c->D.H * kv.bs >= 1LL << 31) return 0;   // rows are numbered in 32 bits
-  const int want = std::max(1, 4 * c->cus / (rm.nseq * c->D.H));
-  const int fit = (c->max_ctx + kMfMinTokens - 1) / kMfMinTokens;          // splits of at least kMfMinTokens
-  const int need = (c->max_ctx + kMfMaxTokens - 1) / kMfMaxTokens;
-  const int S = std::max(need, std::min(want, fit));
-  return S <= 63 && S <= c->lay.S_max ? S : 0;
-}
+// Passes on the plane-fed projections (tp_kernels.h): 3 and more rows, bf16 weights.
+bool tp_pass(const m2r2_ctx* c, const RowMap& rm) { return c->ws.XB && rm.M > 2; }
 
-template <int WB, int HD>
-void mf_launch(const m2r2_ctx* c, const LayerPtrs& L, const RowMap& rm, const StepIO& io, const KVPtrs& kv, int l, int S,
-               int rows_per_seq, hipStream_t st) {
-  const dim3 grid(c->D.H, rm.nseq, S);
-  const size_t lds = mf_attn_lds_bytes(c->max_ctx, S);
-  if (rows_per_seq <= 2) km_attn<WB, HD, 2><<<grid, kMfThreads, lds, st>>>(c->D, L, rm, c->ws, io, kv, l, S);
-  else km_attn<WB, HD, 16><<<grid, kMfThreads, lds, st>>>(c->D, L, rm, c->ws, io, kv, l, S);
+// Fast rows of such a pass: none, or those of a dual batch (row 2k + 1 of every pair).
+int fast_rows(const RowMap& rm) { return has_fast_row(rm) ? rm.M / 2 : 0; }
+
+// A wave's share of a reduction of length K, in steps: the instantiation (0: streamed).
+#define M2R2_TP_LAUNCH(NAME, K, T, ...)                                                            \
+  do {                                                                                             \
+    const int per_ = ((K) / 32 + kTpWaves - 1) / kTpWaves;                                         \
+    if (per_ <= 2) NAME<2, MT><<<c->cus, kTpThreads, tp_lds_bytes(T), st>>>(__VA_ARGS__);           \
+    else if (per_ <= 12) NAME<12, MT><<<c->cus, kTpThreads, tp_lds_bytes(T), st>>>(__VA_ARGS__);    \
+    else NAME<0, MT><<<c->cus, kTpThreads, tp_lds_bytes(T), st>>>(__VA_ARGS__);                     \
+  } while (0)
+
+template <int MT>
+void tp_qkv(m2r2_ctx* c, const LayerPtrs& L, const RowMap& rm, const StepIO& io, int l, hipStream_t st) {
+  M2R2_TP_LAUNCH(kt_qkv, c->D.d, kTpTiles, c->D, L, rm, c->ws, io, l, has_fast_row(rm) ? 1 : 0);
 }
+template <int MT>
+void tp_oproj(m2r2_ctx* c, const LayerPtrs& L, const RowMap& rm, const StepIO& io, int l, hipStream_t st) {
+  M2R2_TP_LAUNCH(kt_oproj, c->D.qdim, 1, c->D, L, rm, c->ws, io, l, fast_rows(rm));
+}
+template <int MT>
+void tp_gateup(m2r2_ctx* c, const LayerPtrs& L, const RowMap& rm, const StepIO& io, int l, hipStream_t st) {
+  M2R2_TP_LAUNCH(kt_gateup, c->D.d, kTpTiles, c->D, L, rm, c->ws, io, l, fast_rows(rm));
+}
+template <int MT>
+void tp_down(m2r2_ctx* c, const LayerPtrs& L, const RowMap& rm, const StepIO& io, int l, int nl, hipStream_t st) {
+  const float* next = l + 1 < nl ? c->layers[l + 1].attn_norm : c->final_norm;
+  M2R2_TP_LAUNCH(kt_down, c->D.F, 1, c->D, L, rm, c->ws, io, l, next);
+}
+template <int MT>
+void tp_head(m2r2_ctx* c, const RowMap& rm, const StepIO& io, const KVPtrs& kv, int nl, hipStream_t st) {
+  M2R2_TP_LAUNCH(kt_head, c->D.d, kTpTiles, c->D, c->lm_head, rm, c->ws, io, kv, c->lay.TV, nl);
+}
+#undef M2R2_TP_LAUNCH
 
 template <int WB, int KB, int HD, int MT>
 m2r2_status run_layers_t(m2r2_ctx* c, const RowMap& rm, const StepIO& io, const KVPtrs& kv, int n_layers_run,
@@ -774,11 +824,14 @@ m2r2_status run_layers_t(m2r2_ctx* c, const RowMap& rm, const StepIO& io, const 
   const size_t smem = attn_smem_bytes();
   // M2R2_ATTN_CHUNKS asks for the short-chain attention
   const int SM = c->attn_chunks ? 0 : mf_splits(c, rm, kv, rows_per_seq);
-  const Grids G = grids<WB, MT>(c);
+  constexpr bool TP = WB && MT > 2;   // (the context's planes exist: dense, bf16 weights)
+  Grids G{};
+  if constexpr (!TP) G = grids<WB, MT>(c);
   HIP_TRY(arla_after<WB>(c, io, -1, st));   // the first interval's restart state
   for (int l = 0; l < n_layers_run; ++l) {
     const LayerPtrs& L = c->layers[l];
-    TIMED(0, (k_qkv<WB, MT><<<G.qkv, kGemvThreads, G.l_d, st>>>(D, L, rm, c->ws, io, l)));
+    if constexpr (TP) TIMED(0, (tp_qkv<MT>(c, L, rm, io, l, st)));
+    else TIMED(0, (k_qkv<WB, MT><<<G.qkv, kGemvThreads, G.l_d, st>>>(D, L, rm, c->ws, io, l)));
     if (SM > 0)
       TIMED(1, (mf_launch<WB, HD>(c, L, rm, io, kv, l, SM, rows_per_seq, st)));
     else if (short_attn && S2 > 0 && NCA == 4)
@@ -792,12 +845,19 @@ m2r2_status run_layers_t(m2r2_ctx* c, const RowMap& rm, const StepIO& io, const 
                                        sk_attn_lds_bytes(HD, D.r, WB), st>>>(D, L, rm, c->ws, io, kv, l, c->sk_attn_S)));
     else
       TIMED(1, (k_attn<KB, HD><<<dim3(S + 1, D.H, rm.nseq), kAttnThreads, smem, st>>>(D, L, rm, c->ws, io, kv, l, S)));
-    TIMED(2, (k_oproj<WB, MT><<<G.o, kGemvThreads, G.l_q, st>>>(D, L, rm, c->ws, io, l)));
-    TIMED(3, (k_gateup<WB, MT><<<G.gu, kGemvThreads, G.l_d, st>>>(D, L, rm, c->ws, io, l)));
-    TIMED(4, (k_down<WB, MT><<<G.o, kGemvThreads, G.l_f, st>>>(D, L, rm, c->ws, io, l)));
+    if constexpr (TP) {
+      TIMED(2, (tp_oproj<MT>(c, L, rm, io, l, st)));
+      TIMED(3, (tp_gateup<MT>(c, L, rm, io, l, st)));
+      TIMED(4, (tp_down<MT>(c, L, rm, io, l, n_layers_run, st)));
+    } else {
+      TIMED(2, (k_oproj<WB, MT><<<G.o, kGemvThreads, G.l_q, st>>>(D, L, rm, c->ws, io, l)));
+      TIMED(3, (k_gateup<WB, MT><<<G.gu, kGemvThreads, G.l_d, st>>>(D, L, rm, c->ws, io, l)));
+      TIMED(4, (k_down<WB, MT><<<G.o, kGemvThreads, G.l_f, st>>>(D, L, rm, c->ws, io, l)));
+    }
     HIP_TRY(arla_after<WB>(c, io, l, st));
   }
-  TIMED(5, (k_head<WB, MT><<<G.head, kGemvThreads, G.l_d, st>>>(D, c->lm_head, c->final_norm, rm, c->ws, io, kv,
+  if constexpr (TP) TIMED(5, (tp_head<MT>(c, rm, io, kv, n_layers_run, st)));
+  else TIMED(5, (k_head<WB, MT><<<G.head, kGemvThreads, G.l_d, st>>>(D, c->lm_head, c->final_norm, rm, c->ws, io, kv,
                                                               c->lay.TV, n_layers_run)));
   HIP_TRY(hipGetLastError());
   return M2R2_OK;
@@ -824,12 +884,33 @@ m2r2_status run_hd(m2r2_ctx* c, const RowMap& rm, const StepIO& io, const KVPtrs
 
 // Pack the projection matrices of every layer and the LM head into the
 // workspace (null stream).
-hipError_t pack_one(int wb, PackSrc src, int rows, int K, void* dst) {
+hipError_t pack_one(int wb, PackSrc src, int rows, int K, void* dst, int th = 16) {
+  if (th != 16) {
+    const size_t pieces = (size_t)((rows + th - 1) / th) * (K / 32) * 4 * th;
+    k_pack_th<<<(int)std::min<size_t>(8192, (pieces + 255) / 256), 256>>>(src, rows, K, th, dst);
+    return hipGetLastError();
+  }
   const size_t chunks = (size_t)((rows + 15) / 16) * (K / (wb ? 32 : 16)) * 64;
   const int grid = (int)std::min<size_t>(8192, (chunks + 255) / 256);
   if (wb) k_pack<1><<<grid, 256>>>(src, rows, K, dst);
   else k_pack<0><<<grid, 256>>>(src, rows, K, dst);
   return hipGetLastError();
+}
+
+// Rows of a packed tile: 16, or 12 where the matrix then spreads more evenly
+// over the compute units (the longest workgroup's rows, counted below) and the
+// packed copy of q/k/v, o and down serves the passes of 3 and more rows alone
+// (one- and two-row passes on the row-per-wave kernels; the others read tiles
+// of 16).  d = 3072 over 256 compute units: 12 rows each instead of 16 on 192.
+void choose_tiles(m2r2_ctx* c) {
+  Dims& D = c->D;
+  auto rows = [&](int n, int th) { return (n / th + c->cus - 1) / c->cus * th; };
+  auto pick = [&](int n, int unit) {
+    return D.wbf16 && !is_moe(c->cfg) && c->rw_on && unit % 12 == 0 && rows(n, 12) < rows(n, 16) ? 12 : 16;
+  };
+  D.th_qkv = pick(3 * D.qdim, D.qdim);
+  D.th_o = pick(D.d, D.d);
+  D.th_d = pick(D.d, D.d);
 }
 
 hipError_t pack_all(m2r2_ctx* c, const m2r2_weights* w, void* workspace) {
@@ -841,11 +922,11 @@ hipError_t pack_all(m2r2_ctx* c, const m2r2_weights* w, void* workspace) {
   for (int l = 0; l < cf.n_layers && e == hipSuccess; ++l) {
     const m2r2_layer_weights& L = w->layers[l];
     const size_t* o = &c->lay.lay_off[8 * l];
-    e = pack_one(wb, one(L.wq, q), q, d, b + o[0]);
-    if (e == hipSuccess) e = pack_one(wb, one(L.wk, q), q, d, b + o[1]);
-    if (e == hipSuccess) e = pack_one(wb, one(L.wv, q), q, d, b + o[2]);
-    if (e == hipSuccess) e = pack_one(wb, PackSrc{{L.A[0], L.A[1], L.A[2]}, {r, r, r}}, 3 * r, d, b + o[3]);
-    if (e == hipSuccess) e = pack_one(wb, one(L.wo, d), d, q, b + o[4]);
+    e = pack_one(wb, one(L.wq, q), q, d, b + o[0], c->D.th_qkv);
+    if (e == hipSuccess) e = pack_one(wb, one(L.wk, q), q, d, b + o[1], c->D.th_qkv);
+    if (e == hipSuccess) e = pack_one(wb, one(L.wv, q), q, d, b + o[2], c->D.th_qkv);
+    if (e == hipSuccess) e = pack_one(wb, PackSrc{{L.A[0], L.A[1], L.A[2]}, {r, r, r}}, 3 * r, d, b + o[3], c->D.th_qkv);
+    if (e == hipSuccess) e = pack_one(wb, one(L.wo, d), d, q, b + o[4], c->D.th_o);
     if (is_moe(cf)) {
       if (e == hipSuccess) e = pack_one(wb, one(L.router, cf.n_experts), cf.n_experts, d, b + o[5]);
       continue;
@@ -857,7 +938,7 @@ hipError_t pack_all(m2r2_ctx* c, const m2r2_weights* w, void* workspace) {
       else k_pack_pair<0><<<grid, 256>>>(L.wg, L.wu, F, d, b + o[5]);
       e = hipGetLastError();
     }
-    if (e == hipSuccess) e = pack_one(wb, one(L.wd, d), d, F, b + o[7]);
+    if (e == hipSuccess) e = pack_one(wb, one(L.wd, d), d, F, b + o[7], c->D.th_d);
   }
   if (e == hipSuccess) e = pack_one(wb, one(w->lm_head, cf.vocab), cf.vocab, d, b + c->lay.lm);
   return e;
@@ -1111,7 +1192,8 @@ m2r2_status run_pk(m2r2_ctx* c, const RowMap& rm, const StepIO& io, const KVPtrs
 // Embedding, n_layers_run layers, head (one launch where the shape allows).
 m2r2_status run_pass(m2r2_ctx* c, const RowMap& rm, const StepIO& io, const KVPtrs& kv, int nl, hipStream_t st) {
   if (pk_eligible(c, rm, io)) return run_pk(c, rm, io, kv, nl, st);
-  TIMED(6, (k_embed<<<rm.M + kEmbedZeroBlocks, 256, 0, st>>>(c->D, c->embed, rm, c->ws, io, 1)));
+  TIMED(6, (k_embed<<<rm.M + kEmbedZeroBlocks, kEmbedThreads, 0, st>>>(c->D, c->embed, rm, c->ws, io, 1,
+                                                               tp_pass(c, rm) ? c->layers[0].attn_norm : nullptr)));
   HIP_TRY(hipGetLastError());
   const int wb = c->D.wbf16, kb = c->D.kvbf16;
   if (wb && kb) return run_hd<1, 1>(c, rm, io, kv, nl, st);
@@ -1443,7 +1525,7 @@ m2r2_status run_moe_pass(m2r2_ctx* c, const RowMap& rm, const StepIO& io, const 
   const int N = c->D.n_layers, K = c->moe.K;
   if (out->slow_experts_d) HIP_TRY(hipMemsetAsync(out->slow_experts_d, 0xff, sizeof(int32_t) * N * K, st));
   if (out->pred_experts_d) HIP_TRY(hipMemsetAsync(out->pred_experts_d, 0xff, sizeof(int32_t) * N * K, st));
-  TIMED(6, (k_embed<<<rm.M + kEmbedZeroBlocks, 256, 0, st>>>(c->D, c->embed, rm, c->ws, io, 1)));
+  TIMED(6, (k_embed<<<rm.M + kEmbedZeroBlocks, kEmbedThreads, 0, st>>>(c->D, c->embed, rm, c->ws, io, 1, nullptr)));
   HIP_TRY(hipGetLastError());
   const int wb = c->D.wbf16, kb = c->D.kvbf16;
   if (wb && kb) return run_moe_hd<1, 1>(c, rm, io, kv, out, dual, st);
@@ -1641,6 +1723,9 @@ M2R2_API m2r2_status m2r2_create(const m2r2_config* cfg, const m2r2_weights* w, 
   ws.lm_idx = (int*)(b + lay.lm_idx); ws.lm_cnt = (uint32_t*)(b + lay.lm_cnt); ws.exited = (int*)(b + lay.exited);
   ws.exitb = (int*)(b + lay.exitb); ws.reinit = (int*)(b + lay.reinit); ws.err = (int*)(b + lay.err);
   ws.sig = (float*)(b + lay.sig);
+  if (lay.plane_bytes) {
+    ws.XB = (uint16_t*)(b + lay.XB); ws.OB = (uint16_t*)(b + lay.OB); ws.AB = (uint16_t*)(b + lay.AB);
+  }
   ws.arla_kv = (float*)(b + lay.arla_kv); ws.arla_q = (float*)(b + lay.arla_q);
   ws.arla_sig = (float*)(b + lay.arla_sig); ws.arla_cnt = (uint32_t*)(b + lay.arla_cnt);
   ws.rope = (const float2*)(b + lay.rope);
@@ -1667,15 +1752,16 @@ M2R2_API m2r2_status m2r2_create(const m2r2_config* cfg, const m2r2_weights* w, 
       }
     e = hipMemcpy(b + lay.rope, t.data(), t.size() * sizeof(float), hipMemcpyHostToDevice);
   }
-  if (e == hipSuccess) e = pack_all(c, w, workspace);
   if (e == hipSuccess) e = set_lds_limits<0, 2>(*cfg, c->resident);
   if (e == hipSuccess) e = set_lds_limits<1, 2>(*cfg, c->resident);
   if (e == hipSuccess) e = set_lds_limits<0, 8>(*cfg, c->resident);
-  if (e == hipSuccess) e = set_lds_limits<1, 8>(*cfg, c->resident);
   if (e == hipSuccess) e = set_lds_limits<0, 16>(*cfg, c->resident);
-  if (e == hipSuccess) e = set_lds_limits<1, 16>(*cfg, c->resident);
   if (e == hipSuccess) e = sk_setup(c);
   if (e == hipSuccess) e = pk_setup(c);
+  if (e == hipSuccess) {
+    choose_tiles(c);
+    e = pack_all(c, w, workspace);
+  }
   if (e == hipSuccess && is_flops(*cfg)) e = fattn_set_lds((int)fattn_lds_bytes(max_ctx));
   if (e == hipSuccess && moe) {
     MoeState& M = c->moe;
@@ -1899,6 +1985,7 @@ struct ScratchRebase {
     w.att_cnt = rb(w.att_cnt); w.lm_val = rb(w.lm_val); w.lm_idx = rb(w.lm_idx); w.lm_cnt = rb(w.lm_cnt);
     w.exited = rb(w.exited); w.exitb = rb(w.exitb); w.reinit = rb(w.reinit); w.sig = rb(w.sig);
     w.arla_kv = rb(w.arla_kv); w.arla_q = rb(w.arla_q); w.arla_sig = rb(w.arla_sig); w.arla_cnt = rb(w.arla_cnt);
+    w.XB = rb(w.XB); w.OB = rb(w.OB); w.AB = rb(w.AB);
     w.fsc = rb(w.fsc); w.fqkv = rb(w.fqkv); w.lrz = rb(w.lrz);
     c->skws.part = rb(c->skws.part); c->skws.hier = rb(c->skws.hier); c->skws.cnt = rb(c->skws.cnt);
     c->pk.sd = rb(c->pk.sd); c->pk.so = rb(c->pk.so); c->pk.sgu = rb(c->pk.sgu); c->pk.bar = rb(c->pk.bar); c->pk.rel = rb(c->pk.rel);
@@ -1934,7 +2021,7 @@ M2R2_API m2r2_status m2r2_decode_step_noalloc(m2r2_ctx* c, int32_t batch, int32_
   HIP_TRY(hipGetDevice(&dev));
   if (dev != c->device)
     return fail(M2R2_E_STATE, "context created on device %d, but device %d is current", c->device, dev);
-  const size_t need = c->lay.scratch_end - c->lay.scratch_begin;
+  const size_t need = c->lay.scratch_end - c->lay.scratch_begin - c->lay.plane_bytes;
   if (need > kNoAllocScratchBytes)
     return fail(M2R2_E_SHAPE, "the context's per-call scratch needs %zu bytes, above the static maximum of %zu "
                               "(create the context with a smaller max_batch or max_ctx)", need, kNoAllocScratchBytes);

@@ -438,7 +438,7 @@ __global__ __launch_bounds__(kSkAttnThreads) void ks_attn(Dims D, LayerPtrs L, R
       v += mw[ei][u] * ld_agent(ws.att + (pbase + (size_t)u * kMaxRows + ei) * (2 + HD + r) + 2 + ed);
     v *= linv[ei];
     q_s[ei][ed] = v;   // o of row ei (q is no longer needed)
-    ws.O[(size_t)(first + ei) * qd + h * HD + ed] = v;
+    put_o(D, rm, ws, first + ei, h * HD + ed, v);
   }
   __syncthreads();
   // o-adapter down-projection share of this head: uo[row][h][j] = sum_d A_o[j][h*HD + d] o[d]

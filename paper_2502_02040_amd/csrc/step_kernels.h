@@ -36,6 +36,7 @@ struct Dims {
   // fast heads kept, positions each attends to, adapter-only fast MLP, rank
   // of the fast row's head
   int fh, ftk, fmlp, hr;
+  int th_qkv, th_o, th_d;   // rows of a packed tile of q/k/v, o, down (passes of 3 and more rows, bf16 weights)
 };
 
 // Projection matrices are read from a tile-packed copy (pack_index below):
@@ -90,6 +91,9 @@ struct WS {
   float* QKV;      // [16][nqkv]    q|k|v|u_q|u_k|u_v (already divided by rms)
   float* O;        // [16][qdim]    attention output
   float* ACT;      // [16][F]       SwiGLU activation
+  // the same in matrix operand order, bf16 hi and lo parts (passes of 3 and
+  // more rows, bf16 weights): X times the next norm's gain, O, ACT
+  uint16_t *XB, *OB, *AB;
   // Row statistics and adapter-down projections are sums over a whole row,
   // which the producing kernel holds in 16-row tiles.  Each workgroup adds its
   // tile's share with float atomics into one of kBins bins of the layer; the
@@ -175,6 +179,16 @@ __device__ __forceinline__ bool is_gate(const StepIO& io, int b) {
 
 __device__ __forceinline__ int row_pos(const RowMap& rm, const StepIO& io, int m) {
   return io.positions[rm.seq[m]] + rm.pos_offset + rm.idx[m];
+}
+
+// Store element k of row m: hi and lo bf16 parts in operand order,
+// [k/32][hi, lo][(k%32)/8][16 rows][8].
+__device__ __forceinline__ void tp_put(uint16_t* planes, int m, int k, float v) {
+  const uint32_t h = f32_to_bf16_bits(v);
+  const uint32_t l = f32_to_bf16_bits(v - __uint_as_float(h << 16));
+  uint16_t* p = planes + (size_t)(k >> 5) * 1024 + ((k >> 3) & 3) * 128 + m * 8 + (k & 7);
+  p[0] = (uint16_t)h;
+  p[512] = (uint16_t)l;
 }
 
 // ============================================================================
@@ -988,25 +1002,26 @@ __global__ __launch_bounds__(256) void k_pack_pair(const void* wg, const void* w
 
 // ============================================================================
 // Kernel: embedding gather + per-step control initialisation + zeroed bins.
-// grid = M rows + kEmbedZeroBlocks, block = 256.  Block m < M gathers row m
+// grid = M rows + kEmbedZeroBlocks, block = kEmbedThreads.  Block m < M gathers row m
 // and writes its layer-0 bins (every slot); the other blocks zero the bins
 // of every later layer (all slots, the M rows in use).
 // ============================================================================
-constexpr int kEmbedZeroBlocks = 64;
+constexpr int kEmbedZeroBlocks = 64, kEmbedThreads = 512;
 
-__global__ __launch_bounds__(256) void k_embed(Dims D, const void* embed, RowMap rm, WS ws, StepIO io, int init_ctl) {
-  __shared__ float red[4];
+__global__ __launch_bounds__(kEmbedThreads) void k_embed(Dims D, const void* embed, RowMap rm, WS ws, StepIO io, int init_ctl,
+                                               const float* gain0) {
+  __shared__ float red[kEmbedThreads / 64];
   if ((int)blockIdx.x >= rm.M) {
     // zero bin_d of layers 1..n_layers, bin_o and bin_gu: every (layer, slot)
     // block holds kMaxRows rows of nv values, of which rows < M are used
     const int nvs[3] = {4, 1 + 2 * D.r, D.r};
     float* bases[3] = {ws.bin_d + (size_t)kBinSlots * kMaxRows * 4, ws.bin_o, ws.bin_gu};
     const int nblk = D.n_layers * kBinSlots;
-    const int stride = (gridDim.x - rm.M) * 256;
+    const int stride = (gridDim.x - rm.M) * kEmbedThreads;
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
       const int used = rm.M * nvs[a], n = nblk * used;
-      for (int i = (blockIdx.x - rm.M) * 256 + threadIdx.x; i < n; i += stride) {
+      for (int i = (blockIdx.x - rm.M) * kEmbedThreads + threadIdx.x; i < n; i += stride) {
         const int blk = i / used;
         bases[a][(size_t)blk * kMaxRows * nvs[a] + (i - blk * used)] = 0.f;
       }
@@ -1018,15 +1033,17 @@ __global__ __launch_bounds__(256) void k_embed(Dims D, const void* embed, RowMap
   const bool ok = tok >= 0 && tok < D.V;
   if (!ok && threadIdx.x == 0) atomicOr(ws.err, 1);
   float ss = 0.f;
-  for (int i = threadIdx.x; i < D.d; i += 256) {
+#pragma unroll 4
+  for (int i = threadIdx.x; i < D.d; i += kEmbedThreads) {
     const float v = ok ? ld_w(embed, (size_t)tok * D.d + i, D.wbf16) : 0.f;
     ws.X[m * D.d + i] = v;
     ws.PIN[m * D.d + i] = v;
+    if (gain0) tp_put(ws.XB, m, i, v * gain0[i]);   // (layer 0's norm gain)
     ss += v * v;
   }
   ss = block_sum(ss, red);
   // layer-0 bins of this row: slot 0 holds the sums, the other slots zero
-  for (int i = threadIdx.x; i < kBinSlots * 4; i += 256) {
+  for (int i = threadIdx.x; i < kBinSlots * 4; i += kEmbedThreads) {
     const int b = i / 4, c = i % 4;
     bin_d_at(ws, 0, b, m)[c] = (b == 0 && c < 3) ? ss : 0.f;
   }
@@ -1295,6 +1312,13 @@ __device__ __forceinline__ float* att_part(const WS& ws, const Dims& D, int s, i
   return ws.att + ((((size_t)s * D.H + h) * (n_split + 1) + sp) * kMaxRows + i) * stride;
 }
 
+// Attention output element k of row m (in operand order too where the o
+// projection reads it so).
+__device__ __forceinline__ void put_o(const Dims& D, const RowMap& rm, const WS& ws, int m, int k, float v) {
+  ws.O[(size_t)m * D.qdim + k] = v;
+  if (ws.OB && rm.M > 2) tp_put(ws.OB, m, k, v);
+}
+
 // Merge the partials of one (sequence, head): the output o of every row and,
 // for fast rows, the o-adapter down-projection of that head.  The partials
 // were written by other workgroups: device-coherent loads.
@@ -1340,7 +1364,7 @@ __device__ __forceinline__ void attn_merge(const Dims& D, const RowMap& rm, cons
     }
     v *= linv[i];
     const int mi = first + i;
-    if (c < D.hd) ws.O[(size_t)mi * D.qdim + h * D.hd + c] = v;
+    if (c < D.hd) put_o(D, rm, ws, mi, h * D.hd + c, v);
     else ws.uo[((size_t)mi * D.H + h) * D.r + (c - D.hd)] = rm.fast[mi] ? v : 0.f;
   }
 }
@@ -2096,6 +2120,87 @@ __global__ __launch_bounds__(kGemvThreads) void k_down(Dims D, LayerPtrs L, RowM
   tg.run(n_local, ptr, epi);
 }
 
+// The last workgroup of a head launch: global arg-max per head row over the
+// n_tiles partials, then the step's bookkeeping (tokens, exit state, acceptance
+// of a verified chunk).  ssum: the rows' statistics after the last layer;
+// copy_states: h_out and p_out are this workgroup's to write.
+__device__ __forceinline__ void head_finish(const Dims& D, const RowMap& rm, const RowMap& rml, const WS& ws,
+                                            const StepIO& io, const KVPtrs& kv, int n_tiles, int nh,
+                                            const float* ssum, bool copy_states = true) {
+  const int lane = threadIdx.x & 63;
+  __shared__ int best_s[kMaxRows];
+  const int wave = threadIdx.x >> 6;
+  for (int k = wave; k < nh; k += kGemvWaves) {
+    float bz = -INFINITY;
+    int bi = 0x7fffffff;
+#pragma unroll 4
+    for (int t = lane; t < n_tiles; t += 64) {
+      const float z = ld_agent(&ws.lm_val[(size_t)t * kMaxRows + k]);
+      const int i = ld_agent(&ws.lm_idx[(size_t)t * kMaxRows + k]);
+      if (z > bz || (z == bz && i < bi)) { bz = z; bi = i; }
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+      const float z2 = __shfl_xor(bz, o);
+      const int i2 = __shfl_xor(bi, o);
+      if (z2 > bz || (z2 == bz && i2 < bi)) { bz = z2; bi = i2; }
+    }
+    if (lane == 0) best_s[k] = bi;
+  }
+  __syncthreads();
+  if (rm.head_all) {
+    // chunk verification / prefill (one sequence)
+    if (threadIdx.x == 0) {
+      const int t = io.positions[0];
+      for (int k = 0; k < nh; ++k) io.targets[k] = best_s[k];
+      int keep = nh;
+      if (io.n_acc) {
+        int j = 0;
+        while (j < nh - 1 && io.tokens[j + 1] == best_s[j]) ++j;
+        io.n_acc[0] = j;
+        if (io.bonus) io.bonus[0] = best_s[j];
+        keep = j + 1;
+      }
+      kv.seq_lens[0] = t + keep;
+      io.positions[0] = t + keep;
+    }
+    return;
+  }
+  // decode step / draft step
+  for (int sq = threadIdx.x; sq < rm.nseq; sq += kGemvThreads) {
+    const int f = rml.first[sq] + rml.cnt[sq] - 1;
+    io.next_token[sq + io.draft_slot] = best_s[sq];
+    const int t = io.positions[sq] + rm.pos_offset;
+    if (rml.slow_of[f] >= 0 || !rml.fast[f]) kv.seq_lens[sq] = t + 1;
+    if (rml.fast[f] && rml.slow_of[f] >= 0) {
+      // signal of the last layer
+      const float dot = ssum[f * 4 + 1], pin2 = ssum[f * 4 + 2], pp = ssum[f * 4 + 0];
+      ws.sig[sq * D.n_layers + D.n_layers - 1] = ws.exited[sq] ? 0.f : dot * rsqrtf(fmaxf(pin2 * pp, 1e-30f));
+    }
+    if (io.exit_b_out) io.exit_b_out[sq] = ws.exitb[sq];
+    if (io.advance) io.positions[sq] = io.positions[sq] + 1;
+  }
+  __syncthreads();
+  if (io.signal_out) {
+    for (int q = threadIdx.x; q < rm.nseq * D.n_layers; q += kGemvThreads) {
+      const int sq = q / D.n_layers, l = q % D.n_layers;
+      const int f = rml.first[sq] + rml.cnt[sq] - 1;
+      float v = ws.sig[q];
+      // layers after an exit were not run
+      if (!rml.fast[f] || rml.slow_of[f] < 0 || (ws.exited[sq] && l >= ws.exitb[sq])) v = 0.f;
+      io.signal_out[q] = v;
+    }
+  }
+  if (copy_states && (io.h_out || io.p_out)) {
+    for (int q = threadIdx.x; q < rm.nseq * D.d; q += kGemvThreads) {
+      const int sq = q / D.d, i = q % D.d;
+      const int f = rml.first[sq], c = rml.cnt[sq];
+      if (io.h_out) io.h_out[q] = ws.X[(size_t)f * D.d + i];
+      if (io.p_out) io.p_out[q] = ws.X[(size_t)(f + c - 1) * D.d + i];
+    }
+  }
+}
+
 // ============================================================================
 // Kernel: final norm + LM head + argmax; the last workgroup to finish takes
 // the global arg-max and finishes the step (tokens, exit bookkeeping,
@@ -2117,7 +2222,6 @@ __global__ __launch_bounds__(kGemvThreads) void k_head(Dims D, const void* lm_he
   const RowMap& rml = rmu.rm;
   if ((int)blockIdx.x >= n_tiles) return;
   using TG = TileGemv<WB, MT>;
-  const int lane = threadIdx.x & 63;
   const size_t tb = (size_t)16 * D.d * (WB ? 2 : 4);
   auto tile_ptr = [&](int t) -> const char* { return (const char*)lm_head + (size_t)t * tb; };
   auto ptr = [&](int i) { return tile_ptr(blockIdx.x + i * gridDim.x); };
@@ -2208,77 +2312,7 @@ __global__ __launch_bounds__(kGemvThreads) void k_head(Dims D, const void* lm_he
   tg.run(n_local, ptr, epi);
   if (!arrive_last(ws.lm_cnt, gridDim.x, &last_flag)) return;
 
-  // ---- last workgroup: global argmax per head row, then bookkeeping ----------
-  __shared__ int best_s[kMaxRows];
-  const int wave = threadIdx.x >> 6;
-  for (int k = wave; k < nh; k += kGemvWaves) {
-    float bz = -INFINITY;
-    int bi = 0x7fffffff;
-    for (int t = lane; t < n_tiles; t += 64) {
-      const float z = ld_agent(&ws.lm_val[(size_t)t * kMaxRows + k]);
-      const int i = ld_agent(&ws.lm_idx[(size_t)t * kMaxRows + k]);
-      if (z > bz || (z == bz && i < bi)) { bz = z; bi = i; }
-    }
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-      const float z2 = __shfl_xor(bz, o);
-      const int i2 = __shfl_xor(bi, o);
-      if (z2 > bz || (z2 == bz && i2 < bi)) { bz = z2; bi = i2; }
-    }
-    if (lane == 0) best_s[k] = bi;
-  }
-  __syncthreads();
-  if (rm.head_all) {
-    // chunk verification / prefill (one sequence)
-    if (threadIdx.x == 0) {
-      const int t = io.positions[0];
-      for (int k = 0; k < nh; ++k) io.targets[k] = best_s[k];
-      int keep = nh;
-      if (io.n_acc) {
-        int j = 0;
-        while (j < nh - 1 && io.tokens[j + 1] == best_s[j]) ++j;
-        io.n_acc[0] = j;
-        if (io.bonus) io.bonus[0] = best_s[j];
-        keep = j + 1;
-      }
-      kv.seq_lens[0] = t + keep;
-      io.positions[0] = t + keep;
-    }
-    return;
-  }
-  // decode step / draft step
-  for (int sq = threadIdx.x; sq < rm.nseq; sq += kGemvThreads) {
-    const int f = rml.first[sq] + rml.cnt[sq] - 1;
-    io.next_token[sq + io.draft_slot] = best_s[sq];
-    const int t = io.positions[sq] + rm.pos_offset;
-    if (rml.slow_of[f] >= 0 || !rml.fast[f]) kv.seq_lens[sq] = t + 1;
-    if (rml.fast[f] && rml.slow_of[f] >= 0) {
-      // signal of the last layer
-      const float dot = ssum[f * 4 + 1], pin2 = ssum[f * 4 + 2], pp = ssum[f * 4 + 0];
-      ws.sig[sq * D.n_layers + D.n_layers - 1] = ws.exited[sq] ? 0.f : dot * rsqrtf(fmaxf(pin2 * pp, 1e-30f));
-    }
-    if (io.exit_b_out) io.exit_b_out[sq] = ws.exitb[sq];
-    if (io.advance) io.positions[sq] = io.positions[sq] + 1;
-  }
-  __syncthreads();
-  if (io.signal_out) {
-    for (int q = threadIdx.x; q < rm.nseq * D.n_layers; q += kGemvThreads) {
-      const int sq = q / D.n_layers, l = q % D.n_layers;
-      const int f = rml.first[sq] + rml.cnt[sq] - 1;
-      float v = ws.sig[q];
-      // layers after an exit were not run
-      if (!rml.fast[f] || rml.slow_of[f] < 0 || (ws.exited[sq] && l >= ws.exitb[sq])) v = 0.f;
-      io.signal_out[q] = v;
-    }
-  }
-  if (io.h_out || io.p_out) {
-    for (int q = threadIdx.x; q < rm.nseq * D.d; q += kGemvThreads) {
-      const int sq = q / D.d, i = q % D.d;
-      const int f = rml.first[sq], c = rml.cnt[sq];
-      if (io.h_out) io.h_out[q] = ws.X[(size_t)f * D.d + i];
-      if (io.p_out) io.p_out[q] = ws.X[(size_t)(f + c - 1) * D.d + i];
-    }
-  }
+  head_finish(D, rm, rml, ws, io, kv, n_tiles, nh, ssum);
 }
 
 }  // namespace m2r2
