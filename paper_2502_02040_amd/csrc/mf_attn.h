@@ -83,6 +83,145 @@ __device__ __forceinline__ float mf_group_sum(float v) {
   return __uint_as_float(b[0]) + __uint_as_float(b[1]);
 }
 
+// One wave's share of a head's attention: up to 16 queries (lane % 16) over
+// tiles of 32 tokens.
+template <int HD>
+struct MfWave {
+  static constexpr int NS = HD / 32;   // matrix steps of a score
+  static constexpr int ND = HD / 8;    // lanes n that hold dims
+  struct Tile {
+    u32x4_t k[2][NS], v[8];
+  };
+  u32x4_t qh[NS], qm[NS], ql[NS];
+  float m_run, l_run;   // running maximum of the lane's query, sum over the lane's tokens
+  f32x4_t acc[8];       // dim 8 (4 g + i) + j of query q: acc[j][i]
+
+  // q: 8 consecutive floats per step, dims 32 s + 8 g .. (16-byte aligned); zero where not live
+  __device__ __forceinline__ void init(const float* q, bool live) {
+    const int g = (threadIdx.x & 63) >> 4;
+#pragma unroll
+    for (int s = 0; s < NS; ++s) {
+      const float4 a = *(const float4*)(q + 32 * s + 8 * g), b = *(const float4*)(q + 32 * s + 8 * g + 4);
+      float x[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
+#pragma unroll
+      for (int i = 0; i < 8; ++i) x[i] = live ? x[i] : 0.f;
+      mf_split3(x, qh[s], qm[s], ql[s]);
+    }
+    m_run = -INFINITY;
+    l_run = 0.f;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) acc[j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  }
+
+  static __device__ __forceinline__ u32x4_t ldc(const char* p) {
+    return *(const __attribute__((address_space(1))) u32x4_t*)p;
+  }
+  // tr: cache rows of the tile's 32 tokens; kb, vb: this layer's pages
+  static __device__ __forceinline__ void load(const uint32_t* tr, const char* kb, const char* vb, Tile& t) {
+    load_k(tr, kb, t);
+    load_v(tr, vb, t);
+  }
+  static __device__ __forceinline__ void load_k(const uint32_t* tr, const char* kb, Tile& t) {
+    const int q = threadIdx.x & 15, g = (threadIdx.x & 63) >> 4;
+#pragma unroll
+    for (int a = 0; a < 2; ++a) {
+      const char* p = kb + (size_t)tr[16 * a + q] * (HD * 2) + 16 * g;
+#pragma unroll
+      for (int s = 0; s < NS; ++s) t.k[a][s] = ldc(p + 64 * s);
+    }
+  }
+  static __device__ __forceinline__ void load_v(const uint32_t* tr, const char* vb, Tile& t) {
+    const int q = threadIdx.x & 15, g = (threadIdx.x & 63) >> 4;
+#pragma unroll
+    for (int a = 0; a < 2; ++a) {
+      const u32x4_t rows = *(const u32x4_t*)(tr + 16 * a + 4 * g);
+#pragma unroll
+      for (int x = 0; x < 4; ++x) t.v[4 * a + x] = ldc(vb + (size_t)rows[x] * (HD * 2) + 16 * min(q, ND - 1));
+    }
+  }
+
+  // see(t): whether the lane's query sees token t of the tile; keys_done()
+  // runs once the tile's keys are no longer needed
+  template <class See>
+  __device__ __forceinline__ void tile(const Tile& t, float scale, See see) {
+    tile(t, scale, see, [] {});
+  }
+  template <class See, class Done>
+  __device__ __forceinline__ void tile(const Tile& t, float scale, See see, Done keys_done) {
+    const int g = (threadIdx.x & 63) >> 4;
+    f32x4_t s0 = {0.f, 0.f, 0.f, 0.f}, s1 = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int s = 0; s < NS; ++s) {
+      s0 = mf_mma(t.k[0][s], ql[s], s0);
+      s1 = mf_mma(t.k[1][s], ql[s], s1);
+    }
+#pragma unroll
+    for (int s = 0; s < NS; ++s) {
+      s0 = mf_mma(t.k[0][s], qm[s], s0);
+      s1 = mf_mma(t.k[1][s], qm[s], s1);
+    }
+#pragma unroll
+    for (int s = 0; s < NS; ++s) {
+      s0 = mf_mma(t.k[0][s], qh[s], s0);
+      s1 = mf_mma(t.k[1][s], qh[s], s1);
+    }
+    keys_done();
+    float z[8], mx = -INFINITY;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const int tok = (i < 4 ? 0 : 16) + 4 * g + (i & 3);
+      z[i] = see(tok) ? (i < 4 ? s0[i & 3] : s1[i & 3]) * scale : -INFINITY;
+      mx = fmaxf(mx, z[i]);
+    }
+    const float mn = fmaxf(m_run, mf_group_max(mx));
+    const float al = m_run == -INFINITY ? 0.f : __expf(m_run - mn);
+    m_run = mn;
+    float p[8], ls = 0.f;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      p[i] = z[i] == -INFINITY ? 0.f : __expf(z[i] - mn);
+      ls += p[i];
+    }
+    l_run = l_run * al + ls;
+    if (__any(al != 1.f)) {
+#pragma unroll
+      for (int j = 0; j < 8; ++j) acc[j] *= al;
+    }
+    u32x4_t ph, pm, pl;
+    mf_split3(p, ph, pm, pl);
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      // dim 8 n + j of the lane's eight tokens
+      u32x4_t vt;
+#pragma unroll
+      for (int w = 0; w < 4; ++w)
+        vt[w] = __builtin_amdgcn_perm(t.v[2 * w + 1][j >> 1], t.v[2 * w][j >> 1], (j & 1) ? 0x07060302u : 0x05040100u);
+      acc[j] = mf_mma(vt, pl, acc[j]);
+      acc[j] = mf_mma(vt, pm, acc[j]);
+      acc[j] = mf_mma(vt, ph, acc[j]);
+    }
+  }
+
+  // Query q's maximum and sum, and its accumulators (HD floats at `out`, 16-byte aligned).
+  __device__ __forceinline__ void store(bool live, float* m, float* l, float* out) {
+    const int g = (threadIdx.x & 63) >> 4;
+    const float ls = mf_group_sum(l_run);
+    if (!live) return;
+    if (g == 0) {
+      *m = m_run;
+      *l = ls;
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int n = 4 * g + i;
+      if (n < ND) {
+        *(float4*)(out + 8 * n) = make_float4(acc[0][i], acc[1][i], acc[2][i], acc[3][i]);
+        *(float4*)(out + 8 * n + 4) = make_float4(acc[4][i], acc[5][i], acc[6][i], acc[7][i]);
+      }
+    }
+  }
+};
+
 // RMAX: rows of a sequence, at most: 2 (slow and fast row, or one row alone) or 16 (a chunk of slow rows).
 template <int WB, int HD, int RMAX>
 __global__ __launch_bounds__(kMfThreads, 2) void km_attn(Dims D, LayerPtrs L, RowMap rm, WS ws, StepIO io, KVPtrs kv,
@@ -250,29 +389,12 @@ __global__ __launch_bounds__(kMfThreads, 2) void km_attn(Dims D, LayerPtrs L, Ro
   __syncthreads();
   // ---- the first tile's keys and values, in flight while q is formed ---------
   const size_t lay0 = (size_t)layer * kv.num_blocks * D.H * kv.bs;
-  const char* kb = (const char*)kv.k + lay0 * HD * 2 + 16 * g;
-  const char* vb = (const char*)kv.v + lay0 * HD * 2 + 16 * min(q, ND - 1);
-  auto ldc = [](const char* p) {
-    return *(const __attribute__((address_space(1))) u32x4_t*)p;
-  };
-  u32x4_t kr[2][NS], vr[8], kn[2][NS], vn[8];
-  auto load = [&](int tt, u32x4_t (&ka)[2][NS], u32x4_t (&va)[8]) {
-    const uint32_t* tr = trow + tt * kMfTile;
-#pragma unroll
-    for (int a = 0; a < 2; ++a) {
-      const char* p = kb + (size_t)tr[16 * a + q] * (HD * 2);
-#pragma unroll
-      for (int s = 0; s < NS; ++s) ka[a][s] = ldc(p + 64 * s);
-    }
-#pragma unroll
-    for (int a = 0; a < 2; ++a) {
-      const u32x4_t rows = *(const u32x4_t*)(tr + 16 * a + 4 * g);
-#pragma unroll
-      for (int t = 0; t < 4; ++t) va[4 * a + t] = ldc(vb + (size_t)rows[t] * (HD * 2));
-    }
-  };
+  const char* kb = (const char*)kv.k + lay0 * HD * 2;
+  const char* vb = (const char*)kv.v + lay0 * HD * 2;
+  using MW = MfWave<HD>;
+  typename MW::Tile ta, tb;
   int tt = wv;
-  if (!frozen && tt < ntile) load(tt, kr, vr);
+  if (!frozen && tt < ntile) MW::load(trow + tt * kMfTile, kb, vb, ta);
   __builtin_amdgcn_sched_barrier(0);
   // adapter-up of a fast row's pair of projection w (pre: its rows of B, loaded)
   auto adapt = [&](int w, int j, const u32x4_t (&pre)[2][2], float& a, float& b) {
@@ -350,116 +472,34 @@ __global__ __launch_bounds__(kMfThreads, 2) void km_attn(Dims D, LayerPtrs L, Ro
     p = wave_sum(p);
     if (lane == 0) ownf_s = p * scale;
   }
-  // ---- q as the B operand: lane (q, g) holds dims 32 s + 8 g .. + 8 ----------
-  u32x4_t qh[NS], qm[NS], ql[NS];
-#pragma unroll
-  for (int s = 0; s < NS; ++s) {
-    float x[8];
-    const float4 a = *(const float4*)&q_s[q][32 * s + 8 * g], b = *(const float4*)&q_s[q][32 * s + 8 * g + 4];
-    x[0] = a.x; x[1] = a.y; x[2] = a.z; x[3] = a.w; x[4] = b.x; x[5] = b.y; x[6] = b.z; x[7] = b.w;
-    mf_split3(x, qh[s], qm[s], ql[s]);
-  }
-  float m_run = -INFINITY, l_run = 0.f;   // of query q (l: this lane's tokens)
-  f32x4_t acc[8];
-#pragma unroll
-  for (int j = 0; j < 8; ++j) acc[j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-  // one tile; see(t): whether query q sees token t of the tile
-  auto tile = [&](const u32x4_t (&ka)[2][NS], const u32x4_t (&va)[8], auto see) {
-    f32x4_t s0 = {0.f, 0.f, 0.f, 0.f}, s1 = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int s = 0; s < NS; ++s) {
-      s0 = mf_mma(ka[0][s], ql[s], s0);
-      s1 = mf_mma(ka[1][s], ql[s], s1);
-    }
-#pragma unroll
-    for (int s = 0; s < NS; ++s) {
-      s0 = mf_mma(ka[0][s], qm[s], s0);
-      s1 = mf_mma(ka[1][s], qm[s], s1);
-    }
-#pragma unroll
-    for (int s = 0; s < NS; ++s) {
-      s0 = mf_mma(ka[0][s], qh[s], s0);
-      s1 = mf_mma(ka[1][s], qh[s], s1);
-    }
-    float z[8], mx = -INFINITY;
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      const int t = (i < 4 ? 0 : 16) + 4 * g + (i & 3);
-      z[i] = see(t) ? (i < 4 ? s0[i & 3] : s1[i & 3]) * scale : -INFINITY;
-      mx = fmaxf(mx, z[i]);
-    }
-    const float mn = fmaxf(m_run, mf_group_max(mx));
-    const float al = m_run == -INFINITY ? 0.f : __expf(m_run - mn);
-    m_run = mn;
-    float p[8], ls = 0.f;
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      p[i] = z[i] == -INFINITY ? 0.f : __expf(z[i] - mn);
-      ls += p[i];
-    }
-    l_run = l_run * al + ls;
-    if (__any(al != 1.f)) {
-#pragma unroll
-      for (int j = 0; j < 8; ++j) acc[j] *= al;
-    }
-    u32x4_t ph, pm, pl;
-    mf_split3(p, ph, pm, pl);
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      // dim 8 n + j of the lane's eight tokens
-      u32x4_t vt;
-#pragma unroll
-      for (int w = 0; w < 4; ++w)
-        vt[w] = __builtin_amdgcn_perm(va[2 * w + 1][j >> 1], va[2 * w][j >> 1], (j & 1) ? 0x07060302u : 0x05040100u);
-      acc[j] = mf_mma(vt, pl, acc[j]);
-      acc[j] = mf_mma(vt, pm, acc[j]);
-      acc[j] = mf_mma(vt, ph, acc[j]);
-    }
-  };
-  auto cached = [&](int t_of) {
-    const int left = nt - t_of * kMfTile;
-    return [left](int t) { return t < left; };
-  };
+  MW mw_;
+  mw_.init(q_s[q], true);   // (rows beyond the sequence's are zero)
   while (tt < ntile) {
-    if (tt + kMfWaves < ntile) load(tt + kMfWaves, kn, vn);
-    tile(kr, vr, cached(tt));
+    if (tt + kMfWaves < ntile) MW::load(trow + (tt + kMfWaves) * kMfTile, kb, vb, tb);
+    mw_.tile(ta, scale, [left = nt - tt * kMfTile](int t) { return t < left; });
     tt += kMfWaves;
     if (tt >= ntile) break;
-    if (tt + kMfWaves < ntile) load(tt + kMfWaves, kr, vr);
-    tile(kn, vn, cached(tt));
+    if (tt + kMfWaves < ntile) MW::load(trow + (tt + kMfWaves) * kMfTile, kb, vb, ta);
+    mw_.tile(tb, scale, [left = nt - tt * kMfTile](int t) { return t < left; });
     tt += kMfWaves;
   }
   if (own && wv == (ntile & (kMfWaves - 1))) {
     // the rows' own keys: a slow row sees the slow rows up to itself, as cached
 #pragma unroll
     for (int s = 0; s < NS; ++s) {
-      kr[0][s] = *(const u32x4_t*)&ko_s[q][32 * s + 8 * g];
-      kr[1][s] = u32x4_t{0u, 0u, 0u, 0u};
+      ta.k[0][s] = *(const u32x4_t*)&ko_s[q][32 * s + 8 * g];
+      ta.k[1][s] = u32x4_t{0u, 0u, 0u, 0u};
     }
 #pragma unroll
     for (int t = 0; t < 4; ++t) {
-      vr[t] = *(const u32x4_t*)&vo_s[4 * g + t][8 * min(q, ND - 1)];
-      vr[4 + t] = u32x4_t{0u, 0u, 0u, 0u};
+      ta.v[t] = *(const u32x4_t*)&vo_s[4 * g + t][8 * min(q, ND - 1)];
+      ta.v[4 + t] = u32x4_t{0u, 0u, 0u, 0u};
     }
     const bool slow = q < R && q != fast_i;
-    tile(kr, vr, [&](int t) { return slow && t <= q && t != fast_i; });
+    mw_.tile(ta, scale, [&](int t) { return slow && t <= q && t != fast_i; });
   }
   // ---- the waves' results, combined --------------------------------------------
-  l_run = mf_group_sum(l_run);
-  if (g == 0) {
-    m_s[wv][q] = m_run;
-    l_s[wv][q] = l_run;
-  }
-  if (q < R) {
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int n = 4 * g + i;
-      if (n < ND) {
-        *(float4*)&acc_s[wv][q][8 * n] = make_float4(acc[0][i], acc[1][i], acc[2][i], acc[3][i]);
-        *(float4*)&acc_s[wv][q][8 * n + 4] = make_float4(acc[4][i], acc[5][i], acc[6][i], acc[7][i]);
-      }
-    }
-  }
+  mw_.store(q < R, &m_s[wv][q], &l_s[wv][q], acc_s[wv][min(q, RMAX - 1)]);
   __syncthreads();
   const int stride = 2 + HD + r;
   float* part = ws.att + (((size_t)sq * D.H + h) * (S + 1)) * kMaxRows * stride;

@@ -30,6 +30,7 @@
 // bit 16 and runs to the end, so the launch always drains.
 #pragma once
 #include "rw_kernels.h"
+#include "mf_attn.h"
 
 namespace m2r2 {
 
@@ -37,6 +38,7 @@ constexpr int kPkWaves = 8;
 constexpr int kPkThreads = 64 * kPkWaves;
 constexpr int kPkMaxWG = 320;            // statistics slots are sized for up to 320 workgroups
 constexpr int kPkSdW = 8;                // slot floats of the layer-input statistics: rows 0, 1 x (x^2, pin.x, pin^2, 0)
+constexpr int kPkSeg = 1024;     // tokens of a split whose cache rows are held at once (bfloat16 cache)
 constexpr int kPkChunk = 128;            // attention tokens per chunk (4 lanes per token)
 constexpr int kPkMaxSplits = 32;         // attention splits per head
 constexpr uint64_t kPkSpinTicks = 200000000ull;   // grid-barrier time limit: 2 s of the 100 MHz clock
@@ -425,10 +427,14 @@ struct PkShared {
 // of the projection phases are not live during attention).
 template <int HD, int WB>
 struct PkAttLds {
-  float q[2][HD], k[2][HD], v[2][HD];
+  __attribute__((aligned(16))) float q[2][HD], k[2][HD], v[2][HD];
   float u[2][3][kMaxRank];
   float sc[2][2 * kPkChunk + 2];   // a pair of chunks, then the own keys
-  float pvred[32][2][HD];
+  // partial sums of P V (float32 cache), or the waves' accumulators
+  __attribute__((aligned(16))) float pvred[32][2][HD];
+  // bfloat16 cache: the cache rows of a segment of the split, the waves' maxima and sums
+  __attribute__((aligned(16))) uint32_t trow[kPkSeg];
+  float wm[kPkWaves][2], wl[kPkWaves][2];
   float mw[2][kPkMaxSplits], ml[2][kPkMaxSplits];
   float rowm[2], rowl[2], lastw[2], fin_m[2], fin_l[2], linv[2];
   float uop[kMaxRank * (HD / 8)];
@@ -688,12 +694,19 @@ __device__ __forceinline__ void pk_phase_att(int l, uint32_t& target, PkShared& 
       };
       u32x4_t kr[2][NCH], vr[2][NCH];
       const bool work = has && !frozen;
-      if (work) {
-        load_chunk(kv.k, 0, kr[0]);
-        load_chunk(kv.v, 0, vr[0]);
-        load_chunk(kv.k, min(1, nch - 1), kr[1]);
-        load_chunk(kv.v, min(1, nch - 1), vr[1]);
-      }
+      // bfloat16 cache: waves take tiles of 32 tokens on the matrix cores; the
+      // first tile is primed.  Cache rows of tokens seg0.. of the split:
+      using MW = MfWave<HD>;
+      typename MW::Tile ta;
+      const size_t lay0 = (size_t)l * kv.num_blocks * H * kv.bs;
+      const char* kb = (const char*)kv.k + lay0 * HD * KESZ;
+      const char* vb = (const char*)kv.v + lay0 * HD * KESZ;
+      auto fill_rows = [&](int seg0, int n) {   // (the tail of the last tile repeats the last token)
+        for (int j = tid; j < (n + kMfTile - 1) / kMfTile * kMfTile; j += kPkThreads) {
+          const int tp = t0 + seg0 + min(j, n - 1);
+          A.trow[j] = (uint32_t)((blk_of(tp) * H + h) * kv.bs + tp % kv.bs);
+        }
+      };
       const int ppieces = HD * r * WESZ / 16;   // 16-byte pieces per projection (<= 2 per thread)
       u32x4_t bp[3][2];
 #pragma unroll
@@ -705,6 +718,27 @@ __device__ __forceinline__ void pk_phase_att(int l, uint32_t& target, PkShared& 
           const int o = min(tid + kPkThreads * k, ppieces - 1);
           bp[w][k] = (LB[w] && has) ? B[o] : u32x4_t{0u, 0u, 0u, 0u};
         }
+      }
+      auto stage_b = [&]() {
+#pragma unroll
+        for (int w = 0; w < 3; ++w)
+#pragma unroll
+          for (int k = 0; k < 2; ++k) {
+            const int o = tid + kPkThreads * k;
+            if (o < ppieces) ((u32x4_t*)A.bsl)[w * ppieces + o] = bp[w][k];
+          }
+      };
+      if constexpr (KB) {
+        const int n = min(t1 - t0, kPkSeg);
+        if (work) fill_rows(0, n);
+        stage_b();
+        __syncthreads();
+        if (work && wv * kMfTile < n) MW::load(A.trow + wv * kMfTile, kb, vb, ta);
+      } else if (work) {
+        load_chunk(kv.k, 0, kr[0]);
+        load_chunk(kv.v, 0, vr[0]);
+        load_chunk(kv.k, min(1, nch - 1), kr[1]);
+        load_chunk(kv.v, min(1, nch - 1), vr[1]);
       }
       const int apieces = r * HD / 8;
       u32x4_t ap = u32x4_t{0u, 0u, 0u, 0u};
@@ -739,13 +773,7 @@ __device__ __forceinline__ void pk_phase_att(int l, uint32_t& target, PkShared& 
           const int row = min(q / (3 * r), M - 1);
           uv = ld_agent(&P.ws.QKV[(size_t)row * nqkv + 3 * qd + q % (3 * r)]);
         }
-#pragma unroll
-        for (int w = 0; w < 3; ++w)
-#pragma unroll
-          for (int k = 0; k < 2; ++k) {
-            const int o = tid + kPkThreads * k;
-            if (o < ppieces) ((u32x4_t*)A.bsl)[w * ppieces + o] = bp[w][k];
-          }
+        if constexpr (!KB) stage_b();
         if (tid < 2 * 3 * r) A.u[tid / (3 * r)][(tid % (3 * r)) / r][tid % r] = uv;
         __syncthreads();
         // q, k, v: base projection plus the adapter up-projection on the fast row
@@ -806,6 +834,75 @@ __device__ __forceinline__ void pk_phase_att(int l, uint32_t& target, PkShared& 
         }
       }
       if (work) {
+        if constexpr (KB) {
+          // own keys (own split), on waves the tiles leave idle at short splits:
+          // a slow row sees the slow row (its own key, rounded as cached), a
+          // fast row only its own exact key
+          if (wv >= 4) {
+            const int i = (wv - 4) >> 1, jj = wv & 1;
+            float p = -INFINITY;
+            if (own && i < R && jj < R &&
+                (rml.fast[i] ? jj == i : !rml.fast[jj] && rml.idx[jj] <= rml.idx[i])) {
+              p = 0.f;
+              for (int dd = lane; dd < HD; dd += 64) {
+                const float kk = A.k[jj][dd];
+                p += A.q[i][dd] * (rml.fast[i] ? kk : round_bf16(kk));
+              }
+              p = wave_sum(p) * scale;
+            }
+            if (lane == 0) A.sc[i][jj] = p;
+          }
+          MW w;
+          const int qi = lane & 15;
+          w.init(A.q[min(qi, R - 1)], qi < R);
+          for (int seg = 0; seg < t1 - t0; seg += kPkSeg) {
+            const int n = min(t1 - t0 - seg, kPkSeg);
+            if (seg > 0) {
+              __syncthreads();   // the rows of the segment before have been read
+              fill_rows(seg, n);
+              __syncthreads();
+              if (wv * kMfTile < n) MW::load(A.trow + wv * kMfTile, kb, vb, ta);
+            }
+            // the next tile's keys are requested once this one's are scored,
+            // its values once this one's are summed (a second tile in
+            // registers would not fit beside the step's other state)
+            constexpr int STEP = kPkWaves * kMfTile;
+            for (int t = wv * kMfTile; t < n; t += STEP) {
+              const uint32_t* nt = A.trow + t + STEP;
+              const bool more = t + STEP < n;
+              w.tile(ta, scale, [left = n - t](int x) { return x < left; }, [&] { if (more) MW::load_k(nt, kb, ta); });
+              if (more) MW::load_v(nt, vb, ta);
+            }
+          }
+          w.store(qi < R, &A.wm[wv][qi & 1], &A.wl[wv][qi & 1], &A.pvred[wv][qi & 1][0]);
+          __syncthreads();
+          for (int e = tid; e < R * HD; e += kPkThreads) {
+            const int i = e / HD, dd = e % HD;
+            float Mx = own ? fmaxf(A.sc[i][0], A.sc[i][1]) : -INFINITY;
+#pragma unroll
+            for (int x = 0; x < kPkWaves; ++x) Mx = fmaxf(Mx, A.wm[x][i]);
+            float a = 0.f, ls = 0.f;
+#pragma unroll
+            for (int x = 0; x < kPkWaves; ++x) {
+              const float f = A.wl[x][i] > 0.f ? __expf(A.wm[x][i] - Mx) : 0.f;
+              a += f * A.pvred[x][i][dd];
+              ls += f * A.wl[x][i];
+            }
+            if (own) {
+              for (int jj = 0; jj < R; ++jj) {
+                const float f = A.sc[i][jj] == -INFINITY ? 0.f : __expf(A.sc[i][jj] - Mx);
+                a += f * (rml.fast[i] ? A.v[jj][dd] : round_bf16(A.v[jj][dd]));
+                ls += f;
+              }
+            }
+            float* pp = P.ws.att + (((size_t)h * (S + 1) + sp) * kMaxRows + i) * (2 + HD + r);
+            st_agent(pp + 2 + dd, a);
+            if (dd == 0) {
+              st_agent(pp, Mx);
+              st_agent(pp + 1, ls);
+            }
+          }
+        } else {
         float m_run[2] = {-INFINITY, -INFINITY}, l_run[2] = {0.f, 0.f};
         float acc0[DPL], acc1[DPL];
 #pragma unroll
@@ -967,6 +1064,7 @@ __device__ __forceinline__ void pk_phase_att(int l, uint32_t& target, PkShared& 
             st_agent(pp, A.fin_m[i]);
             st_agent(pp + 1, A.fin_l[i]);
           }
+        }
         }
         // ---- every split counts in; the last of the head merges them
         if (arrive_last(&P.ws.att_cnt[h], S, &sh.last_flag)) {

@@ -690,6 +690,24 @@ void mf_launch(const m2r2_ctx* c, const LayerPtrs& L, const RowMap& rm, const St
   else km_attn<WB, HD, 16><<<grid, kMfThreads, lds, st>>>(c->D, L, rm, c->ws, io, kv, l, S);
 }
 
+// Attention of a pass with one or two rows: on the matrix cores where that
+// applies (SM splits), else the short-chain kernel, else (a float32 cache of
+// more than 64 splits) the general one.
+template <int WB, int KB, int HD>
+void attn_launch(const m2r2_ctx* c, const LayerPtrs& L, const RowMap& rm, const StepIO& io, const KVPtrs& kv, int l,
+                 int SM, hipStream_t st) {
+  const Dims& D = c->D;
+  if (SM > 0) {
+    mf_launch<WB, HD>(c, L, rm, io, kv, l, SM, rm.M, st);
+  } else if (c->sk_attn_S) {
+    ks_attn<WB, KB, HD><<<dim3(c->sk_attn_S, D.H, rm.nseq), kSkAttnThreads, sk_attn_lds_bytes(HD, D.r, WB), st>>>(
+        D, L, rm, c->ws, io, kv, l, c->sk_attn_S);
+  } else {
+    const int S = choose_splits(rm.nseq, rm.M, D.H, c->max_ctx);
+    k_attn<KB, HD><<<dim3(S + 1, D.H, rm.nseq), kAttnThreads, attn_smem_bytes(), st>>>(D, L, rm, c->ws, io, kv, l, S);
+  }
+}
+
 // One or two rows: row-per-wave GEMVs and the short-chain attention.
 template <int WB, int KB, int HD>
 m2r2_status run_layers_rw(m2r2_ctx* c, const RowMap& rm, const StepIO& io, const KVPtrs& kv, int n_layers_run,
@@ -702,6 +720,7 @@ m2r2_status run_layers_rw(m2r2_ctx* c, const RowMap& rm, const StepIO& io, const
   // attention: one 128-token chunk per split (two only when M2R2_ATTN_CHUNKS
   // asks for it: measured no faster at one sequence)
   const int S2 = c->attn_chunks == 2 ? (c->max_ctx + 2 * kSkAttnP - 1) / (2 * kSkAttnP) : 0;
+  const int SM = c->attn_chunks ? 0 : mf_splits(c, rm, kv, rm.M);
   HIP_TRY(arla_after<WB>(c, io, -1, st));   // the first interval's restart state
   for (int l = 0; l < n_layers_run; ++l) {
     const LayerPtrs& L = c->layers[l];
@@ -710,8 +729,7 @@ m2r2_status run_layers_rw(m2r2_ctx* c, const RowMap& rm, const StepIO& io, const
       TIMED(1, (ks_attn<WB, KB, HD, 2><<<dim3(S2, D.H, rm.nseq), kSkAttnThreads, sk_attn_lds_bytes(HD, D.r, WB),
                                           st>>>(D, L, rm, c->ws, io, kv, l, S2)));
     else
-      TIMED(1, (ks_attn<WB, KB, HD><<<dim3(c->sk_attn_S, D.H, rm.nseq), kSkAttnThreads,
-                                       sk_attn_lds_bytes(HD, D.r, WB), st>>>(D, L, rm, c->ws, io, kv, l, c->sk_attn_S)));
+      TIMED(1, (attn_launch<WB, KB, HD>(c, L, rm, io, kv, l, SM, st)));
     TIMED(2, (kr_oproj_launch<WB>(nq, c->rw_nw[0], G, lds, st, D, L, rm, c->ws, io, l)));
     TIMED(3, (kr_gateup_launch<WB>(nd, G, lds, st, D, L, rm, c->ws, io, l)));
     TIMED(4, (kr_down_launch<WB>(nf, c->rw_nw[1], G, lds, st, D, L, rm, c->ws, io, l)));
@@ -1067,7 +1085,9 @@ hipError_t sk_setup(m2r2_ctx* c) {
     // short-chain attention
     const int epp = 64 * (D.wbf16 ? 8 : 4);   // elements per 1 KB piece
     const int Ks[3] = {D.d, D.qdim, D.F};
-    bool ok_r = c->sk_attn_S > 0 && (D.r * wsz) % 16 == 0 && D.r * wsz <= kRwMaxBRowBytes &&
+    // (a capacity of more splits than the short-chain attention has: the matrix-core one)
+    const bool ok_m = D.kvbf16 && !is_flops(cf) && (c->max_ctx + kMfMaxTokens - 1) / kMfMaxTokens <= std::min(63, c->lay.S_max);
+    bool ok_r = (c->sk_attn_S > 0 || ok_m) && (D.r * wsz) % 16 == 0 && D.r * wsz <= kRwMaxBRowBytes &&
                 !getenv_zero("M2R2_ROWWAVE");
     for (int i = 0; i < (moe ? 2 : 3); ++i) {
       c->rw_nch[i] = Ks[i] / epp;
@@ -1152,8 +1172,8 @@ hipError_t pk_setup(m2r2_ctx* c) {
   return hipSuccess;
 }
 
-bool pk_eligible(const m2r2_ctx* c, const RowMap& rm, const StepIO& io) {
-  return c->pk.kind >= 0 && !is_flops(c->cfg) && rm.nseq == 1 && rm.M >= 1 && rm.M <= 2 && !rm.head_all && !io.arla_sig &&
+bool pk_eligible(const m2r2_ctx* c, const RowMap& rm, const StepIO& io, const KVPtrs& kv) {
+  return c->pk.kind >= 0 && (long long)kv.num_blocks * c->D.H * kv.bs < 1LL << 31 && !is_flops(c->cfg) && rm.nseq == 1 && rm.M >= 1 && rm.M <= 2 && !rm.head_all && !io.arla_sig &&
          rm.first[0] == 0 && rm.cnt[0] == rm.M;
 }
 
@@ -1191,7 +1211,7 @@ m2r2_status run_pk(m2r2_ctx* c, const RowMap& rm, const StepIO& io, const KVPtrs
 
 // Embedding, n_layers_run layers, head (one launch where the shape allows).
 m2r2_status run_pass(m2r2_ctx* c, const RowMap& rm, const StepIO& io, const KVPtrs& kv, int nl, hipStream_t st) {
-  if (pk_eligible(c, rm, io)) return run_pk(c, rm, io, kv, nl, st);
+  if (pk_eligible(c, rm, io, kv)) return run_pk(c, rm, io, kv, nl, st);
   TIMED(6, (k_embed<<<rm.M + kEmbedZeroBlocks, kEmbedThreads, 0, st>>>(c->D, c->embed, rm, c->ws, io, 1,
                                                                tp_pass(c, rm) ? c->layers[0].attn_norm : nullptr)));
   HIP_TRY(hipGetLastError());
@@ -1343,6 +1363,7 @@ m2r2_status run_moe_t(m2r2_ctx* c, const RowMap& rm, const StepIO& io, const KVP
   const int S = choose_splits(1, rm.M, D.H, c->max_ctx);
   if (S > c->lay.S_max || S + 1 > 64) return fail(M2R2_E_SHAPE, "attention splits exceed the workspace");
   const size_t smem = attn_smem_bytes();
+  const int SM = mf_splits(c, rm, kv, rm.M);
   const size_t gl = gemv_lds_bytes(WB, MT);
   const bool ahead = dual && M.policy == M2R2_MOE_AHEAD_OF_TIME;
   const bool prev = M.policy == M2R2_MOE_PREVIOUS_LAYER;
@@ -1370,8 +1391,7 @@ m2r2_status run_moe_t(m2r2_ctx* c, const RowMap& rm, const StepIO& io, const KVP
     const LayerPtrs& L = c->layers[l];
     if (c->rw_on) {
       TIMED(0, (kr_qkv_launch<WB>(c->rw_nch[0], c->sk_grid, (size_t)kSkMinLds, st, D, L, rm, c->ws, io, l)));
-      TIMED(1, (ks_attn<WB, KB, HD><<<dim3(c->sk_attn_S, D.H, rm.nseq), kSkAttnThreads,
-                                       sk_attn_lds_bytes(HD, D.r, WB), st>>>(D, L, rm, c->ws, io, kv, l, c->sk_attn_S)));
+      TIMED(1, (attn_launch<WB, KB, HD>(c, L, rm, io, kv, l, SM, st)));
       TIMED(2, (kr_oproj_launch<WB>(c->rw_nch[1], c->rw_nw[0], c->sk_grid, (size_t)kSkMinLds, st, D, L, rm, c->ws,
                                     io, l)));
     } else {
