@@ -40,7 +40,8 @@ constexpr int kPkMaxWG = 320;            // statistics slots are sized for up to
 constexpr int kPkSdW = 8;                // slot floats of the layer-input statistics: rows 0, 1 x (x^2, pin.x, pin^2, 0)
 constexpr int kPkSeg = 1024;     // tokens of a split whose cache rows are held at once (bfloat16 cache)
 constexpr int kPkChunk = 128;            // attention tokens per chunk (4 lanes per token)
-constexpr int kPkMaxSplits = 32;         // attention splits per head
+constexpr int kPkMaxSplits = 32;         // attention splits per head, at most
+constexpr int kPkOneSplit = 64;          // contexts of one split
 constexpr uint64_t kPkSpinTicks = 200000000ull;   // grid-barrier time limit: 2 s of the 100 MHz clock
 
 // 1 KB pieces per row -> (pieces per sub-unit, sub-units per row)
@@ -663,7 +664,12 @@ __device__ __forceinline__ void pk_phase_att(int l, uint32_t& target, PkShared& 
       constexpr int NCH = DPL * KESZ / 16;         // 16-byte pieces per lane and token
       constexpr int WESZ = WB ? 2 : 4;
       PkAttLds<HD, WB>& A = *(PkAttLds<HD, WB>*)pk_dyn;
-      const int S = P.S, H = D.H;
+      // small models: a short context is one workgroup's, and a single split
+      // merges nothing (tiny float32 decoder at 16 positions: 78.4 -> 69.2 us per
+      // step; on 6 KB rows the second path costs every context 0.4 %)
+      constexpr bool ONE = ND <= 2;
+      const int H = D.H;
+      const int S = ONE && ctx <= kPkOneSplit ? 1 : P.S;
       const int task = blockIdx.x;
       const bool has = task < H * S;
       const int h = has ? task / S : 0, sp = has ? task % S : 0;
@@ -833,6 +839,22 @@ __device__ __forceinline__ void pk_phase_att(int l, uint32_t& target, PkShared& 
           }
         }
       }
+      // one element of this split's result: the head's output if there is no
+      // other split (it always holds the row's own key), else a partial
+      auto emit = [&](int i, int dd, float a, float mx, float ls) {
+        if (ONE && S == 1) {
+          const float v = a / ls;
+          st_agent(&P.ws.O[(size_t)i * qd + h * HD + dd], v);
+          A.q[i][dd] = v;   // (q is no longer needed)
+          return;
+        }
+        float* pp = P.ws.att + (((size_t)h * (S + 1) + sp) * kMaxRows + i) * (2 + HD + r);
+        st_agent(pp + 2 + dd, a);
+        if (dd == 0) {
+          st_agent(pp, mx);
+          st_agent(pp + 1, ls);
+        }
+      };
       if (work) {
         if constexpr (KB) {
           // own keys (own split), on waves the tiles leave idle at short splits:
@@ -895,12 +917,7 @@ __device__ __forceinline__ void pk_phase_att(int l, uint32_t& target, PkShared& 
                 ls += f;
               }
             }
-            float* pp = P.ws.att + (((size_t)h * (S + 1) + sp) * kMaxRows + i) * (2 + HD + r);
-            st_agent(pp + 2 + dd, a);
-            if (dd == 0) {
-              st_agent(pp, Mx);
-              st_agent(pp + 1, ls);
-            }
+            emit(i, dd, a, Mx, ls);
           }
         } else {
         float m_run[2] = {-INFINITY, -INFINITY}, l_run[2] = {0.f, 0.f};
@@ -1058,16 +1075,12 @@ __device__ __forceinline__ void pk_phase_att(int l, uint32_t& target, PkShared& 
               if (w != 0.f) a += w * (rnd && KB ? round_bf16(A.v[jj][dd]) : A.v[jj][dd]);
             }
           }
-          float* pp = P.ws.att + (((size_t)h * (S + 1) + sp) * kMaxRows + i) * (2 + HD + r);
-          st_agent(pp + 2 + dd, a);
-          if (dd == 0) {
-            st_agent(pp, A.fin_m[i]);
-            st_agent(pp + 1, A.fin_l[i]);
-          }
+          emit(i, dd, a, A.fin_m[i], A.fin_l[i]);
         }
         }
         // ---- every split counts in; the last of the head merges them
-        if (arrive_last(&P.ws.att_cnt[h], S, &sh.last_flag)) {
+        const bool merge = !(ONE && S == 1) && arrive_last(&P.ws.att_cnt[h], S, &sh.last_flag);
+        if (merge) {
           const size_t pbase = ((size_t)h * (S + 1)) * kMaxRows;
           const int me = min(tid, R * S - 1), mi_ = me / S, ms_ = me % S;
           const float* mp = P.ws.att + (pbase + (size_t)ms_ * kMaxRows + mi_) * (2 + HD + r);
@@ -1105,9 +1118,11 @@ __device__ __forceinline__ void pk_phase_att(int l, uint32_t& target, PkShared& 
             for (int u = 8; u < S; ++u)
               v += A.mw[ei][u] * ld_agent(P.ws.att + (pbase + (size_t)u * kMaxRows + ei) * (2 + HD + r) + 2 + ed);
             v *= A.linv[ei];
-            A.q[ei][ed] = v;   // o of row ei (q is no longer needed)
+            A.q[ei][ed] = v;
             st_agent(&P.ws.O[(size_t)ei * qd + h * HD + ed], v);
           }
+        }
+        if (merge || (ONE && S == 1)) {
           __syncthreads();
           // o-adapter down-projection share of this head (fast row):
           // uo[row][h][j] = sum_d A_o[j][h*HD + d] o[d]

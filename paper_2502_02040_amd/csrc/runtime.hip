@@ -833,7 +833,7 @@ m2r2_status run_layers_t(m2r2_ctx* c, const RowMap& rm, const StepIO& io, const 
   // many splits in flight (batched long contexts): two 128-token chunks per
   // split, the second chunk's loads overlapping the first chunk's work
   const int NCA = c->attn_chunks != 0 ? c->attn_chunks
-                  : ((long long)rm.nseq * D.H * c->sk_attn_S >= 8LL * c->sk_grid ? 2 : 1);
+                  : ((long long)rm.nseq * D.H * c->sk_attn_S >= 8LL * c->cus ? 2 : 1);
   const int S2 = short_attn && NCA > 1 ? (c->max_ctx + NCA * kSkAttnP - 1) / (NCA * kSkAttnP) : 0;
   const int S = choose_splits(rm.nseq, rows_per_seq, D.H, c->max_ctx);
   if (!short_attn && S > c->lay.S_max) return fail(M2R2_E_SHAPE, "attention splits exceed the workspace");
@@ -1042,6 +1042,17 @@ hipError_t sk_setup(m2r2_ctx* c) {
   // of its own); the stream-K GEMVs, whose partial slots its layout does not
   // hold, stay off
   const bool moe = is_moe(cf);
+  // Short-chain attention (also of models whose GEMVs are per-tile): fixed
+  // 128-token splits over the cache capacity (at most 64, within the
+  // workspace's partial slots), the head's B rows in at most three 16-byte
+  // pieces per thread, A_o in two.
+  {
+    const int S = (c->max_ctx + kSkAttnP - 1) / kSkAttnP;
+    const int wsz = c->D.wbf16 ? 2 : 4;
+    const bool ok_a = S <= 64 && S <= c->lay.S_max && c->D.hd * c->D.r * wsz <= 2 * kSkAttnThreads * 16 &&
+                      (c->D.hd * c->D.r * wsz) % 16 == 0 && c->D.r * c->D.hd / 8 <= 2 * kSkAttnThreads;
+    c->sk_attn_S = ok_a ? S : 0;
+  }
   const char* env = getenv("M2R2_STREAMK");
   if (env && env[0] == '0') return hipSuccess;
   int dev = 0, cus = 0;
@@ -1068,14 +1079,7 @@ hipError_t sk_setup(m2r2_ctx* c) {
   if (e == hipSuccess) {
     c->sk_on = !moe;
     c->sk_grid = cus;
-    // attention of the stream-K path: fixed 128-token splits over the cache
-    // capacity (at most 64, within the workspace's partial slots), the head's
-    // B rows in at most three 16-byte pieces per thread, A_o in two
-    const int S = (c->max_ctx + kSkAttnP - 1) / kSkAttnP;
     const int wsz = D.wbf16 ? 2 : 4;
-    const bool ok_a = S <= 64 && S <= c->lay.S_max && D.hd * D.r * wsz <= 2 * kSkAttnThreads * 16 &&
-                      (D.hd * D.r * wsz) % 16 == 0 && D.r * D.hd / 8 <= 2 * kSkAttnThreads;
-    c->sk_attn_S = ok_a ? S : 0;
     // M2R2_ATTN_CHUNKS=1, 2 or 4 fixes the chunks per split of the batched
     // attention (tests exercise both forms at small sizes)
     if (const char* ac = getenv("M2R2_ATTN_CHUNKS"))
@@ -1142,7 +1146,13 @@ hipError_t pk_setup(m2r2_ctx* c) {
   if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
   if (e != hipSuccess) return e;
   if (D.r % 4 || 2 + 2 * D.r > 64 || cus < 1 || cus > kPkMaxWG || D.H > cus) return hipSuccess;
-  const int S = std::min(kPkMaxSplits, std::max(1, cus / D.H));
+  // a model whose largest phase is small takes 64 workgroups: the grid barrier
+  // and the sums over the workgroups' slots cost less than the bytes (tiny
+  // float32 decoder, 2 MB phases: 81.4 us per step on 256, 76.9 on 64, 80.4 on 32)
+  const size_t wsz = D.wbf16 ? 2 : 4;
+  const size_t phase = wsz * D.d * std::max({3 * D.qdim, 2 * D.F, D.V});
+  const int grid = phase <= ((size_t)8 << 20) ? std::max(D.H, std::min(cus, 64)) : cus;
+  const int S = std::min(kPkMaxSplits, std::max(1, grid / D.H));
   if (S > c->lay.S_max) return hipSuccess;
   const int nd = c->rw_nch[0], nq = c->rw_nch[1], nf = c->rw_nch[2];
   const size_t lds = pk_lds_bytes(D.hd, D.wbf16, std::max({D.d, D.qdim, D.F}));
@@ -1160,7 +1170,7 @@ hipError_t pk_setup(m2r2_ctx* c) {
   e = hipMemcpy(b + c->lay.layers_d, c->layers.data(), sizeof(LayerPtrs) * D.n_layers, hipMemcpyHostToDevice);
   if (e != hipSuccess) return e;
   c->pk.kind = kind;
-  c->pk.grid = cus;
+  c->pk.grid = grid;
   c->pk.S = S;
   c->pk.lds = lds;
   c->pk.layers_d = (const LayerPtrs*)(b + c->lay.layers_d);

@@ -101,3 +101,24 @@ def test_chunk_attention_context_edges(name, ctx, n):
         t.token(int(targets[i].item()), ref[i], pair.tol, f"row {i}")
     pair.check_cache(0, ctx, ctx + n, t)
     assert int(pos.item()) == ctx + n == int(pair.kv.seq_lens[0].item())
+
+
+@pytest.mark.parametrize("name,ctx,cap", [
+    # one split up to 64 positions, then one per head's share of the workgroups; 256 positions per pass
+    *[("tiny", n, 300) for n in (0, 1, 63, 64, 65, 257)],
+    *[("small_rw", n, 300) for n in (0, 31, 64, 65, 257)],
+    ("small_rw", 1025, 2048),
+    # more than 63 splits of 128 positions; more than 1024 positions per split
+    ("small_rw", 8100, 8200),
+    ("small_rw", 16600, 16700),
+    # matrices of fewer blocks than the stream-K kernels take: short-chain attention with per-tile projections
+    ("hd96_f32cache", 130, 200),
+])
+def test_one_sequence_context_edges(name, ctx, cap):
+    """One sequence's dual step at the edges of the attention's splits."""
+    cfg = (synth.CONFIGS["small_bf16"].replace(name=name, kvdtype="f32") if name == "hd96_f32cache"
+           else synth.CONFIGS[name])
+    pair = Pair(cfg, synth.make_weights(cfg), max_ctx=cap, table_seed=17)
+    t = Tally()
+    batch_step(pair, [ctx], t)
+    assert t.steps == 1
