@@ -1299,6 +1299,14 @@ __device__ __forceinline__ void pk_phase_head(int l, uint32_t& target, PkShared&
     st.begin_all(row_ptr, u0, u1, epi, ops);
     target += 1;
     pk_wait(P.bar, target, P.ws.err, &sh.broken);
+    // h_out and p_out: every row's state is final; a thread per element (one
+    // wave copying both rows at the end of the launch took 10 us)
+    if (P.io.h_out || P.io.p_out) {
+      for (int i = blockIdx.x * kPkThreads + tid; i < d; i += G * kPkThreads) {
+        if (P.io.h_out) P.io.h_out[i] = ld_agent(&P.ws.X[i]);
+        if (P.io.p_out) P.io.p_out[i] = ld_agent(&P.ws.X[(size_t)(M - 1) * d + i]);
+      }
+    }
     constexpr int PM = RwPM<WB, CD::NCH, CD::NS, kPkThreads>::value;
     RwPieces<PM> xp;
     pk_load_rows<PM>(P.ws.X, 0, (M > 1 ? 1 : 0) * d, P.final_norm, d, xp);
@@ -1377,12 +1385,6 @@ __device__ __forceinline__ void pk_phase_head(int l, uint32_t& target, PkShared&
         if (q == D.n_layers - 1 && nl == D.n_layers) v = last_sig;
         if (!sig_on || (sh.ex && q >= sh.eb)) v = 0.f;
         P.io.signal_out[q] = v;
-      }
-    }
-    if (P.io.h_out || P.io.p_out) {
-      for (int i = lane; i < d; i += 64) {
-        if (P.io.h_out) P.io.h_out[i] = ld_agent(&P.ws.X[i]);
-        if (P.io.p_out) P.io.p_out[i] = ld_agent(&P.ws.X[(size_t)f * d + i]);
       }
     }
   }

@@ -860,8 +860,11 @@ __global__ __launch_bounds__(kRwThreads) void kr_head(Dims D, const void* lm_hea
     }
   } epi{&D, hrow, inv_rms, io.logits_out, 0, {-INFINITY, -INFINITY}, {0x7fffffff, 0x7fffffff}};
   typename Epi::Ops ops[decltype(st)::P];
+  HeadStates hs;
+  hs.load(D, rm, ws, io, gridDim.x);
   __builtin_amdgcn_sched_barrier(0);
   st.begin(row_ptr, u0, u1, epi, ops);
+  hs.store(D, rm, ws, io);
   __builtin_amdgcn_sched_barrier(0);
   if (tid < rm.nseq) ex_in[tid] = exv;
   sk_rm_copy(rmu, rm);
@@ -1002,14 +1005,6 @@ __global__ __launch_bounds__(kRwThreads) void kr_head(Dims D, const void* lm_hea
       }
       if (!rml.fast[f] || rml.slow_of[f] < 0 || (ws.exited[sq] && l >= ws.exitb[sq])) v = 0.f;
       io.signal_out[q] = v;
-    }
-  }
-  if (io.h_out || io.p_out) {
-    for (int q = lane; q < rm.nseq * D.d; q += 64) {
-      const int sq = q / D.d, i = q % D.d;
-      const int f = rml.first[sq], c = rml.cnt[sq];
-      if (io.h_out) io.h_out[q] = ws.X[(size_t)f * D.d + i];
-      if (io.p_out) io.p_out[q] = ws.X[(size_t)(f + c - 1) * D.d + i];
     }
   }
 }

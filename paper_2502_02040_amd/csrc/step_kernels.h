@@ -2120,6 +2120,46 @@ __global__ __launch_bounds__(kGemvThreads) void k_down(Dims D, LayerPtrs L, RowM
   tg.run(n_local, ptr, epi);
 }
 
+// h_out and p_out of a decode step: the rows' states before the head (each
+// sequence's first and last row), shared by all workgroups of the head launch.
+// load() before the weights are requested, store() after (one wave copying
+// d = 2048 twice at the end of the launch took 8 us).
+struct HeadStates {
+  int n, e0, step;
+  float h, p;
+  static __device__ __forceinline__ void rows(const RowMap& rm, int sq, int& f, int& l) {
+    f = rm.first[0];   // (uniform selects: the map is a kernel argument)
+    l = rm.first[0] + rm.cnt[0] - 1;
+#pragma unroll
+    for (int i = 1; i < kMaxSeq; ++i)
+      if (sq == i) {
+        f = rm.first[i];
+        l = rm.first[i] + rm.cnt[i] - 1;
+      }
+  }
+  __device__ __forceinline__ void get(const Dims& D, const RowMap& rm, const WS& ws, int e) {
+    int f, l;
+    const int sq = e / D.d, i = e - sq * D.d;
+    rows(rm, sq, f, l);
+    h = ws.X[(size_t)f * D.d + i];
+    p = ws.X[(size_t)l * D.d + i];
+  }
+  // wgs: workgroups that take part (those with a tile)
+  __device__ __forceinline__ void load(const Dims& D, const RowMap& rm, const WS& ws, const StepIO& io, int wgs) {
+    n = !rm.head_all && (io.h_out || io.p_out) ? rm.nseq * D.d : 0;
+    e0 = blockIdx.x * blockDim.x + threadIdx.x;
+    step = wgs * blockDim.x;
+    if (e0 < n) get(D, rm, ws, e0);
+  }
+  __device__ __forceinline__ void store(const Dims& D, const RowMap& rm, const WS& ws, const StepIO& io) {
+    for (int e = e0; e < n; e += step) {
+      if (e != e0) get(D, rm, ws, e);
+      if (io.h_out) io.h_out[e] = h;
+      if (io.p_out) io.p_out[e] = p;
+    }
+  }
+};
+
 // The last workgroup of a head launch: global arg-max per head row over the
 // n_tiles partials, then the step's bookkeeping (tokens, exit state, acceptance
 // of a verified chunk).  ssum: the rows' statistics after the last layer;

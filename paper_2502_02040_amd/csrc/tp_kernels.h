@@ -745,40 +745,13 @@ __global__ __launch_bounds__(kTpThreads, 2) void kt_head(Dims D, const void* lm_
     for (int b = 0; b < kBins; ++b) bv[b] = bin_d_at(ws, n_layers_run, b, q >> 2)[q & 3];
   }
   const int exv = ws.exited[min((int)threadIdx.x, rm.nseq - 1)];
-  // h_out and p_out: this workgroup's share of the states (every sequence's rows: first, last)
-  const int n_out = !rm.head_all && (io.h_out || io.p_out) ? rm.nseq * D.d : 0;
   const int wgs = min((int)gridDim.x, n_tiles);
-  float ho = 0.f, po = 0.f;
-  const int o0 = blockIdx.x * kTpThreads + threadIdx.x;
-  int orow = 0, olast = 0;
-  auto out_rows = [&](int e) {   // (the rows of a sequence: uniform selects, the map is a kernel argument)
-    const int sq = e / D.d;
-    orow = rm.first[0];
-    olast = rm.first[0] + rm.cnt[0] - 1;
-#pragma unroll
-    for (int i = 1; i < kMaxSeq; ++i)
-      if (sq == i) {
-        orow = rm.first[i];
-        olast = rm.first[i] + rm.cnt[i] - 1;
-      }
-  };
-  if (o0 < n_out) {
-    out_rows(o0);
-    ho = ws.X[(size_t)orow * D.d + o0 % D.d];
-    po = ws.X[(size_t)olast * D.d + o0 % D.d];
-  }
+  HeadStates hs;
+  hs.load(D, rm, ws, io, wgs);
   __builtin_amdgcn_sched_barrier(0);
   tc.begin(n_local, ptr);
   sk_rm_copy(rmu, rm);
-  if (o0 < n_out) {
-    if (io.h_out) io.h_out[o0] = ho;
-    if (io.p_out) io.p_out[o0] = po;
-  }
-  for (int e = o0 + wgs * kTpThreads; e < n_out; e += wgs * kTpThreads) {
-    out_rows(e);
-    if (io.h_out) io.h_out[e] = ws.X[(size_t)orow * D.d + e % D.d];
-    if (io.p_out) io.p_out[e] = ws.X[(size_t)olast * D.d + e % D.d];
-  }
+  hs.store(D, rm, ws, io);
   if (threadIdx.x < T * kMaxRows) {
     bz_s[threadIdx.x] = -INFINITY;
     bi_s[threadIdx.x] = 0x7fffffff;
