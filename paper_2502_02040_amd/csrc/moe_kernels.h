@@ -177,48 +177,8 @@ __global__ __launch_bounds__(256) void k_topk(int E, int K, const float* logits,
 // adapter alone: p += (rms(p) * g_mlp . A_m^T) B_m^T, with the adapter-down
 // sums taken from the bins of the o projection; then the partial sums of
 // the next layer's norm and of the exit signal.  grid = ceil(d/256), block = 256.
-// Block `blk` of the fast row's MLP (T threads per block).
-template <int T>
-__device__ __forceinline__ void fast_mlp_block(const Dims& D, const RowMap& rm, const LayerPtrs& L, int layer,
-                                               const WS& ws, int blk) {
-  __shared__ float um[kMaxRank];
-  __shared__ float red[T / 64];
-  const int nn = blk * T + threadIdx.x;
-  const int bin = blk % kBins;
-  for (int m = 0; m < rm.M; ++m) {
-    if (!rm.fast[m]) continue;
-    const bool ex = ws.exited[rm.seq[m]] != 0;
-    if (threadIdx.x < D.r) {
-      float a = 0.f, ss = 0.f;
-      for (int b = 0; b < kBinSlots; ++b) {
-        a += bin_o_at(ws, D, layer, b, m)[1 + threadIdx.x];
-        ss += bin_o_at(ws, D, layer, b, m)[0];
-      }
-      um[threadIdx.x] = a * rsqrtf(ss / D.d + D.eps);
-    }
-    __syncthreads();
-    float x = 0.f, p = 0.f;
-    if (nn < D.d) {
-      x = ws.X[(size_t)m * D.d + nn];
-      p = ws.PIN[(size_t)m * D.d + nn];
-      if (!ex && L.A[4] && L.B[4]) {
-        x += dot_row(L.B[4], nn, D.r, um, D.wbf16);
-        ws.X[(size_t)m * D.d + nn] = x;
-      }
-    }
-    const float s0 = block_sum(x * x, red);
-    const float s1 = block_sum(p * x, red);
-    const float s2 = block_sum(p * p, red);
-    if (threadIdx.x == 0) {
-      add_agent(bin_d_at(ws, layer + 1, bin, m) + 0, s0);
-      add_agent(bin_d_at(ws, layer + 1, bin, m) + 1, s1);
-      add_agent(bin_d_at(ws, layer + 1, bin, m) + 2, s2);
-    }
-    __syncthreads();
-  }
-}
 __global__ __launch_bounds__(256) void k_fast_mlp(Dims D, RowMap rm, LayerPtrs L, int layer, WS ws) {
-  fast_mlp_block<256>(D, rm, L, layer, ws, blockIdx.x);
+  fast_mlp_block<256>(D, rm, L.A[4] ? L.B[4] : nullptr, layer, ws, blockIdx.x);
 }
 
 // Kernel: the router tiles of up to three tasks (tiles x n_tasks workgroups,
@@ -235,7 +195,7 @@ __global__ __launch_bounds__(kGemvThreads) void k_route(Dims D, int E, RouterTas
   __shared__ int last;
   const int nr = ((E + 15) / 16) * n_tasks;
   if ((int)blockIdx.x >= nr) {
-    fast_mlp_block<kGemvThreads>(D, rm, L, layer, ws, (int)blockIdx.x - nr);
+    fast_mlp_block<kGemvThreads>(D, rm, L.A[4] ? L.B[4] : nullptr, layer, ws, (int)blockIdx.x - nr);
     return;
   }
   router_tile<WB, true>(D, E, t0, t1, t2, n_tasks, ws, blockIdx.x);

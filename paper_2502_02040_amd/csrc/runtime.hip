@@ -617,8 +617,8 @@ hipError_t arla_after(m2r2_ctx* c, const StepIO& io, int l, hipStream_t st) {
 
 // The dual-stream step of one sequence in the FLOPs-optimised form (Sec. 2.5):
 // the split attention leaves the fast row to k_fattn (kept heads, selected
-// positions); with the adapter-only fast MLP, k_fast_mlp applies it and the
-// gate/up and down kernels see the slow row alone; an exited fast row's
+// positions); with the adapter-only fast MLP, the gate/up launch applies it
+// and its rows, and the down kernel, see the slow row alone; an exited fast row's
 // token comes from the low-rank head.
 template <int WB, int KB, int HD>
 m2r2_status run_layers_flops(m2r2_ctx* c, const RowMap& rm, const StepIO& io, const KVPtrs& kv, int n_layers_run,
@@ -635,8 +635,8 @@ m2r2_status run_layers_flops(m2r2_ctx* c, const RowMap& rm, const StepIO& io, co
   const RowMap& rmlp = D.fmlp ? rs : rm;
   for (int l = 0; l < n_layers_run; ++l) {
     const LayerPtrs& L = c->layers[l];
-    // the o projection sums the MLP adapter's down-projection, k_fast_mlp
-    // applies its up factor: both take it in the gate slot ([rank][d], [d][rank])
+    // the o projection sums the MLP adapter's down-projection, the gate/up
+    // launch applies its up factor: both take it in the gate slot ([rank][d], [d][rank])
     LayerPtrs Lo = L;
     if (D.fmlp) {
       Lo.A[4] = c->fmlp_a[l];
@@ -648,8 +648,8 @@ m2r2_status run_layers_flops(m2r2_ctx* c, const RowMap& rm, const StepIO& io, co
     if (fattn)
       TIMED(1, (k_fattn<KB, HD><<<fh, kFaThreads, fattn_lds_bytes(c->max_ctx), st>>>(D, L, rm, c->ws, io, kv, l)));
     TIMED(2, (kr_oproj_launch<WB>(nq, c->rw_nw[0], G, lds, st, D, Lo, rm, c->ws, io, l)));
-    if (D.fmlp) TIMED(10, (k_fast_mlp<<<(D.d + 255) / 256, 256, 0, st>>>(D, rm, Lo, l, c->ws)));
-    TIMED(3, (kr_gateup_launch<WB>(nd, G, lds, st, D, L, rmlp, c->ws, io, l)));
+    TIMED(3, (kr_gateup_launch<WB>(nd, G, lds, st, D, L, rmlp, c->ws, io, l,
+                                   (int)(D.fmlp != 0), Lo.A[4] ? Lo.B[4] : (const void*)nullptr, rm)));
     TIMED(4, (kr_down_launch<WB>(nf, c->rw_nw[1], G, lds, st, D, L, rmlp, c->ws, io, l)));
   }
   if (D.hr > 0)
@@ -731,7 +731,7 @@ m2r2_status run_layers_rw(m2r2_ctx* c, const RowMap& rm, const StepIO& io, const
     else
       TIMED(1, (attn_launch<WB, KB, HD>(c, L, rm, io, kv, l, SM, st)));
     TIMED(2, (kr_oproj_launch<WB>(nq, c->rw_nw[0], G, lds, st, D, L, rm, c->ws, io, l)));
-    TIMED(3, (kr_gateup_launch<WB>(nd, G, lds, st, D, L, rm, c->ws, io, l)));
+    TIMED(3, (kr_gateup_launch<WB>(nd, G, lds, st, D, L, rm, c->ws, io, l, 0, (const void*)nullptr, rm)));
     TIMED(4, (kr_down_launch<WB>(nf, c->rw_nw[1], G, lds, st, D, L, rm, c->ws, io, l)));
     HIP_TRY(arla_after<WB>(c, io, l, st));
   }
@@ -1890,8 +1890,8 @@ M2R2_API m2r2_status m2r2_time_gateup_layers(m2r2_ctx* c, int32_t dual, hipStrea
   HIP_TRY(hipEventCreate(&b));
   hipError_t e = hipEventRecord(a, st);
   for (int l = 0; l < D.n_layers && e == hipSuccess; ++l) {
-    if (D.wbf16) kr_gateup_launch<1>(c->rw_nch[0], c->sk_grid, (size_t)kSkMinLds, st, D, c->layers[l], rm, c->ws, io, l);
-    else kr_gateup_launch<0>(c->rw_nch[0], c->sk_grid, (size_t)kSkMinLds, st, D, c->layers[l], rm, c->ws, io, l);
+    if (D.wbf16) kr_gateup_launch<1>(c->rw_nch[0], c->sk_grid, (size_t)kSkMinLds, st, D, c->layers[l], rm, c->ws, io, l, 0, (const void*)nullptr, rm);
+    else kr_gateup_launch<0>(c->rw_nch[0], c->sk_grid, (size_t)kSkMinLds, st, D, c->layers[l], rm, c->ws, io, l, 0, (const void*)nullptr, rm);
     e = hipGetLastError();
   }
   if (e == hipSuccess) e = hipEventRecord(b, st);

@@ -632,7 +632,8 @@ __global__ __launch_bounds__(64 * NW) void kr_oproj(Dims D, LayerPtrs L, RowMap 
 // up row j (2j + 1); the epilogue of pair j runs after its up row.
 // ============================================================================
 template <int WB, int NCH, int NS>
-__global__ __launch_bounds__(kRwThreads) void kr_gateup(Dims D, LayerPtrs L, RowMap rm, WS ws, StepIO io, int layer) {
+__global__ __launch_bounds__(kRwThreads) void kr_gateup(Dims D, LayerPtrs L, RowMap rm, WS ws, StepIO io, int layer,
+                                                        int fast_on, const void* fast_b, RowMap rmf) {
   extern __shared__ __attribute__((aligned(16))) float actf[];
   __shared__ float stat[2 * (1 + 2 * kMaxRank)];
   __shared__ float inv_rms[2];
@@ -641,7 +642,14 @@ __global__ __launch_bounds__(kRwThreads) void kr_gateup(Dims D, LayerPtrs L, Row
   __shared__ SkRmLds rmu;
   const RowMap& rml = rmu.rm;
   const int tid = threadIdx.x, gw = blockIdx.x * kRwWaves + __builtin_amdgcn_readfirstlane(tid >> 6);
-  if (io.mode == EX_EXIT && sk_all_exited(rm, ws)) return;
+  // FLOPs-optimised form: the first workgroups also run the fast row's
+  // adapter-only MLP (row map rmf, up factor fast_b), whose row no other part of
+  // this launch reads (a launch of its own took 6 us per layer)
+  const bool fast_wg = fast_on && (int)blockIdx.x * kRwThreads < D.d;
+  if (io.mode == EX_EXIT && sk_all_exited(rm, ws)) {
+    if (fast_wg) fast_mlp_block<kRwThreads>(D, rmf, fast_b, layer, ws, blockIdx.x);
+    return;
+  }
   const int esz = WB ? 2 : 4, r = D.r, PO = 1 + 2 * r;
   auto row_ptr = [&](int hu, int) -> const void* {
     return (const char*)((hu & 1) ? L.wu : L.wg) + (size_t)(hu >> 1) * D.d * esz;
@@ -706,6 +714,7 @@ __global__ __launch_bounds__(kRwThreads) void kr_gateup(Dims D, LayerPtrs L, Row
   __builtin_amdgcn_sched_barrier(0);
   sk_rm_copy(rmu, rm);
   sk_bins_sum(rm.M * PO, sv, actf, stat);
+  if (fast_wg) fast_mlp_block<kRwThreads>(D, rmf, fast_b, layer, ws, blockIdx.x);
   if (tid < 2) inv_rms[tid] = rsqrtf(stat[min(tid, rm.M - 1) * PO] / D.d + D.eps);
   rw_store_pieces<true>(xp, D.d, actf);
   st.run(row_ptr, u0, u1, actf, D.d, epi, ops);

@@ -1081,6 +1081,48 @@ __device__ void gate_logic(const Dims& D, const RowMap& rm, const int* ex_in, co
   }
 }
 
+// Block `blk` of a fast row's adapter-only MLP: x += B_m (rms(x) g_mlp . A_m^T),
+// the adapter-down sums from the o projection's bins, and the sums for the next
+// layer's norm and the exit signal (Bm: [d][rank], null: x is unchanged; T threads).
+template <int T>
+__device__ __forceinline__ void fast_mlp_block(const Dims& D, const RowMap& rm, const void* Bm, int layer,
+                                               const WS& ws, int blk) {
+  __shared__ float um[kMaxRank];
+  __shared__ float red[T / 64];
+  const int nn = blk * T + threadIdx.x;
+  const int bin = blk % kBins;
+  for (int m = 0; m < rm.M; ++m) {
+    if (!rm.fast[m]) continue;
+    const bool ex = ws.exited[rm.seq[m]] != 0;
+    if (threadIdx.x < D.r) {
+      float a = 0.f, ss = 0.f;
+      for (int b = 0; b < kBinSlots; ++b) {
+        a += bin_o_at(ws, D, layer, b, m)[1 + threadIdx.x];
+        ss += bin_o_at(ws, D, layer, b, m)[0];
+      }
+      um[threadIdx.x] = a * rsqrtf(ss / D.d + D.eps);
+    }
+    __syncthreads();
+    float x = 0.f, p = 0.f;
+    if (nn < D.d) {
+      x = ws.X[(size_t)m * D.d + nn];
+      p = ws.PIN[(size_t)m * D.d + nn];
+      if (!ex && Bm) {
+        x += dot_row(Bm, nn, D.r, um, D.wbf16);
+        ws.X[(size_t)m * D.d + nn] = x;
+      }
+    }
+    const float s0 = block_sum(x * x, red);
+    const float s1 = block_sum(p * x, red);
+    const float s2 = block_sum(p * p, red);
+    if (threadIdx.x == 0) {
+      add_agent(bin_d_at(ws, layer + 1, bin, m) + 0, s0);
+      add_agent(bin_d_at(ws, layer + 1, bin, m) + 1, s1);
+      add_agent(bin_d_at(ws, layer + 1, bin, m) + 2, s2);
+    }
+    __syncthreads();
+  }
+}
 // uo_s[m][j] = sum over heads h (in order) of uo[m][h][j] for every fast row
 // m: the o-adapter's down-projection, summed over the heads, all rows at
 // once (every thread one (row, j) pair, its loads independent).  Read after
