@@ -805,6 +805,19 @@ void tp_gateup(m2r2_ctx* c, const LayerPtrs& L, const RowMap& rm, const StepIO& 
 template <int MT>
 void tp_down(m2r2_ctx* c, const LayerPtrs& L, const RowMap& rm, const StepIO& io, int l, int nl, hipStream_t st) {
   const float* next = l + 1 < nl ? c->layers[l + 1].attn_norm : c->final_norm;
+  if constexpr (MT > 8) {
+    // reductions too long to keep a wave's share in registers, in quarters of
+    // at most 8 steps per wave; partial sums in q/k/v's, o's and the fp32
+    // activations' scratch, which nothing holds across this launch
+    const int K = c->D.F, groups = ((c->D.d + c->D.th_d - 1) / c->D.th_d + kTpTiles - 1) / kTpTiles;
+    const size_t bytes = sizeof(float) * groups * kTpDownSplit * kTpDownPart;
+    if (K > 12 * 32 * kTpWaves && K % (32 * kTpWaves * kTpDownSplit) == 0 && K <= 8 * 32 * kTpWaves * kTpDownSplit &&
+        bytes <= c->lay.bin_d - c->lay.QKV && groups <= kMaxSeq * c->D.H) {
+      kt_down_split<8, MT><<<(groups + 1) / 2 * 8, kTpThreads, tp_lds_bytes(kTpTiles), st>>>(c->D, L, rm, c->ws, io, l,
+                                                                                           next, c->ws.QKV);
+      return;
+    }
+  }
   M2R2_TP_LAUNCH(kt_down, c->D.F, 1, c->D, L, rm, c->ws, io, l, next);
 }
 template <int MT>

@@ -1,6 +1,8 @@
 """Batched decoding and chunks at the sizes where their kernels can go wrong
 (rows, ranks and context lengths at the edges of tiles and splits), against
 the oracle under the rule of ``gpu_harness``."""
+import copy
+
 import numpy as np
 import pytest
 import torch
@@ -11,9 +13,11 @@ from tests.gpu_harness import Pair, Tally
 pytestmark = pytest.mark.gpu
 
 
-def batch_step(pair: Pair, lens, t: Tally, *, tol=None, seed=3):
+def batch_step(pair: Pair, lens, t: Tally, *, tol=None, seed=3, mode="observe", gates=None, pick=None):
     """One dual step of sequences with random cache content of the given
-    lengths: logits, h, p, signal, token and the new cache entries."""
+    lengths: logits, h, p, signal, token and the new cache entries.  EXIT mode:
+    pick(sorted signals at the first gate) is the threshold.  Returns how many
+    sequences exited."""
     cfg, B, dev, tol = pair.cfg, len(lens), pair.dev, tol or pair.tol
     N = cfg.n_layers
     for s, n in enumerate(lens):
@@ -25,21 +29,30 @@ def batch_step(pair: Pair, lens, t: Tally, *, tol=None, seed=3):
     out = {k: torch.zeros(B * n, dtype=torch.float32, device=dev)
            for k, n in (("signal", N), ("logits", cfg.vocab), ("h_out", cfg.d_model), ("p_out", cfg.d_model))}
     nxt = torch.zeros(B, dtype=torch.int32, device=dev)
-    gates = list(range(1, N))
+    gates, tau = gates or list(range(1, N)), 0.9
+    if pick:
+        obs = [pair.orc.decode_step(int(toks[s]), n, copy.deepcopy(pair.caches[s]), gates=gates, tau=2.0,
+                                    mode="observe") for s, n in enumerate(lens)]
+        tau = pick(sorted(r.signal[gates[0] - 1] for r in obs))
+        assert all(abs(r.signal[b - 1] - tau) > tol for r in obs for b in gates), "no clear threshold"
+    exits = 0
     pair.model.decode_step(torch.tensor(toks, dtype=torch.int32, device=dev),
-                           torch.tensor(lens, dtype=torch.int32, device=dev), pair.kv.desc(), gates=gates, tau=0.9,
-                           mode="observe", next_token=nxt, **out)
+                           torch.tensor(lens, dtype=torch.int32, device=dev), pair.kv.desc(), gates=gates, tau=tau,
+                           mode=mode, next_token=nxt, **out)
     torch.cuda.synchronize()
     got = {k: v.cpu().numpy().reshape(B, -1) for k, v in out.items()}
     for s, n in enumerate(lens):
-        r = pair.orc.decode_step(int(toks[s]), n, pair.caches[s], gates=gates, tau=0.9, mode="observe")
+        r = pair.orc.decode_step(int(toks[s]), n, pair.caches[s], gates=gates, tau=tau, mode=mode)
+        last = r.exit_boundary if mode == "exit" else N
+        exits += last < N
         t.rel(got["logits"][s], r.logits, tol, f"seq {s} logits")
         t.rel(got["h_out"][s], r.h, tol, f"seq {s} h")
         t.rel(got["p_out"][s], r.p, tol, f"seq {s} p")
-        t.close(got["signal"][s], r.signal, tol, f"seq {s} signal")
+        t.close(got["signal"][s][:last], r.signal[:last], tol, f"seq {s} signal")
         t.token(int(nxt[s].item()), r.logits, tol, f"seq {s} token")
         pair.check_cache(s, n, n + 1, t, f"seq {s}")
         t.steps += 1
+    return exits
 
 
 @pytest.mark.parametrize("rank,B", [(16, 8), (32, 4), (32, 8)])
@@ -119,6 +132,54 @@ def test_one_sequence_context_edges(name, ctx, cap):
     cfg = (synth.CONFIGS["small_bf16"].replace(name=name, kvdtype="f32") if name == "hd96_f32cache"
            else synth.CONFIGS[name])
     pair = Pair(cfg, synth.make_weights(cfg), max_ctx=cap, table_seed=17)
+    t = Tally()
+    batch_step(pair, [ctx], t)
+    assert t.steps == 1
+
+
+@pytest.mark.parametrize("name", ["small_bf16", "small_rw"])
+@pytest.mark.parametrize("lens", [(5, 40, 17), (130, 1, 64, 33, 90, 12, 7, 257)])
+def test_batch_exits(name, lens):
+    """EXIT mode with every sequence, and with a part of them, gone at a gate:
+    their skipped layers' keys and values come from the slow row, their rows
+    stay as they are, and the others go on."""
+    cfg = synth.CONFIGS[name]
+    n = len(lens)
+    widest = lambda v: max(range(n - 1), key=lambda i: v[i + 1] - v[i])   # noqa: E731
+    for pick, gates, want in ((lambda v: -2.0, [1], lambda e: e == n),
+                              (lambda v: (v[widest(v)] + v[widest(v) + 1]) / 2, [2], lambda e: 0 < e < n)):
+        pair = Pair(cfg, synth.make_weights(cfg), max_ctx=max(lens) + 20, max_batch=n, n_seqs=n, table_seed=19)
+        t = Tally()
+        # the least tolerance that decides every signal here: 2^-8 is one bfloat16 rounding
+        assert want(batch_step(pair, lens, t, tol=2.0 ** -8, mode="exit", gates=gates, pick=pick))
+        assert t.steps == n
+
+
+@pytest.mark.parametrize("ffn", [3072, 4096, 5120, 8192])
+@pytest.mark.parametrize("d,B", [(192, 5), (224, 8), (512, 7)])
+def test_long_down_reductions(ffn, d, B):
+    """Down projections of 9 and more rows whose reduction is split over
+    workgroups (and one that is not): tiles in whole groups of four, a group of
+    two, an odd number of groups."""
+    cfg = synth.CONFIGS["small_bf16"].replace(name=f"ffn{ffn}_{d}", d_model=d, ffn=ffn, n_layers=2)
+    pair = Pair(cfg, synth.make_weights(cfg), max_ctx=80, max_batch=B, n_seqs=B, table_seed=23)
+    t = Tally()
+    batch_step(pair, [3, 40, 17, 0, 65, 33, 9, 21][:B], t)
+    batch_step(pair, [4, 41, 18, 1, 66, 34, 10, 22][:B], t)   # counters back at zero
+    assert t.steps == 2 * B
+
+
+@pytest.mark.parametrize("name,ctx,block_size", [
+    *[("tiny", n, 16) for n in (0, 1, 63, 64, 65)],
+    *[("small_rw", n, 16) for n in (0, 1, 63, 64, 65, 200)],
+    ("small_rw", 600, 1),      # block tables of more entries than the selection kernel has threads
+])
+def test_flops_whole_selection(name, ctx, block_size):
+    """The FLOPs-optimised form with a selection that keeps every position (no
+    ties to decide), at the edges of the selected positions' passes of 64."""
+    cfg = synth.CONFIGS[name].replace(name=f"{name}_all", fast_heads=2, fast_topk=4096, fast_mlp_adapter=True,
+                                      head_rank=16)
+    pair = Pair(cfg, synth.make_weights(cfg), max_ctx=ctx + 20, block_size=block_size, table_seed=29)
     t = Tally()
     batch_step(pair, [ctx], t)
     assert t.steps == 1
