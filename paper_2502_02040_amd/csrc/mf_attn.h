@@ -64,6 +64,9 @@ __device__ __forceinline__ void mf_split3(const float (&x)[8], u32x4_t& h, u32x4
   }
 }
 
+// Infinite or NaN (bf16 bits)?
+__device__ __forceinline__ bool mf_odd(uint32_t b) { return (b & 0x7f80u) == 0x7f80u; }
+
 __device__ __forceinline__ f32x4_t mf_mma(u32x4_t a, u32x4_t b, f32x4_t c) {
   return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, a), __builtin_bit_cast(bf16x8_t, b), c,
                                                  0, 0, 0);
@@ -247,7 +250,7 @@ __global__ __launch_bounds__(kMfThreads, 2) void km_attn(Dims D, LayerPtrs L, Ro
   __shared__ u32x4_t ao_s[DUAL ? kMaxRank * (HD / 8) : 1];   // A_o of the head, 8 columns each (bf16 weights)
   __shared__ int bt_s[kMfThreads];                           // first entries of the block table
   __shared__ SkRmLds rmu;
-  __shared__ int last_flag;
+  __shared__ int last_flag, odd_s;   // odd_s: a slow row's own value is infinite or NaN
   const RowMap& rml = rmu.rm;
   const int h = blockIdx.x, sq = blockIdx.y, sp = blockIdx.z;   // working splits are dispatched first
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
@@ -315,6 +318,7 @@ __global__ __launch_bounds__(kMfThreads, 2) void km_attn(Dims D, LayerPtrs L, Ro
   __builtin_amdgcn_sched_barrier(0);
   sk_rm_copy(rmu, rm);
   bt_s[tid] = btv;
+  if (tid == 0) odd_s = 0;
   if constexpr (DUAL) {
     if (tid < 3 * r) u_s[tid] = uv;
     if (WB && fast_i >= 0 && L.A[3]) {
@@ -443,6 +447,7 @@ __global__ __launch_bounds__(kMfThreads, 2) void km_attn(Dims D, LayerPtrs L, Ro
     uint16_t* o = w == 1 ? &ko_s[i][0] : &vo_s[i][0];
     o[j] = (uint16_t)f32_to_bf16_bits(a);
     o[j + HALF] = (uint16_t)f32_to_bf16_bits(b);
+    if (w == 2 && i != fast_i && (mf_odd(o[j]) || mf_odd(o[j + HALF]))) odd_s = 1;
     if (DUAL && i == fast_i) {
       float* f = w == 1 ? kf_s : vf_s;
       f[j] = a;
@@ -492,7 +497,15 @@ __global__ __launch_bounds__(kMfThreads, 2) void km_attn(Dims D, LayerPtrs L, Ro
     }
 #pragma unroll
     for (int t = 0; t < 4; ++t) {
+      // (the products take every row's values, those not seen times zero:
+      // infinities and NaN stay out and are added below where they are seen)
       ta.v[t] = *(const u32x4_t*)&vo_s[4 * g + t][8 * min(q, ND - 1)];
+      if (4 * g + t == fast_i) ta.v[t] = u32x4_t{0u, 0u, 0u, 0u};
+      if (odd_s) {
+#pragma unroll
+        for (int x = 0; x < 4; ++x)
+          ta.v[t][x] &= (mf_odd(ta.v[t][x]) ? 0u : 0xffffu) | (mf_odd(ta.v[t][x] >> 16) ? 0u : 0xffff0000u);
+      }
       ta.v[4 + t] = u32x4_t{0u, 0u, 0u, 0u};
     }
     const bool slow = q < R && q != fast_i;
@@ -516,6 +529,10 @@ __global__ __launch_bounds__(kMfThreads, 2) void km_attn(Dims D, LayerPtrs L, Ro
       const float x = l_s[w][i] > 0.f ? __expf(m_s[w][i] - M) : 0.f;
       a += x * acc_s[w][i][d];
       l += x * l_s[w][i];
+    }
+    if (own && odd_s && i != fast_i) {
+      for (int t = 0; t <= i; ++t)
+        if (t != fast_i && mf_odd(vo_s[t][d])) a += __uint_as_float((uint32_t)vo_s[t][d] << 16);
     }
     if (s_eff == 1) {
       const float o = a / l;

@@ -913,7 +913,7 @@ __device__ __forceinline__ void pk_phase_att(int l, uint32_t& target, PkShared& 
             if (own) {
               for (int jj = 0; jj < R; ++jj) {
                 const float f = A.sc[i][jj] == -INFINITY ? 0.f : __expf(A.sc[i][jj] - Mx);
-                a += f * (rml.fast[i] ? A.v[jj][dd] : round_bf16(A.v[jj][dd]));
+                if (f != 0.f) a += f * (rml.fast[i] ? A.v[jj][dd] : round_bf16(A.v[jj][dd]));
                 ls += f;
               }
             }

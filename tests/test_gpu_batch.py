@@ -183,3 +183,60 @@ def test_flops_whole_selection(name, ctx, block_size):
     t = Tally()
     batch_step(pair, [ctx], t)
     assert t.steps == 1
+
+
+@pytest.mark.parametrize("name", ["hd64", "hd96", "hd128", "tiny"])
+@pytest.mark.parametrize("lens", [(5,), (200,), (5, 200, 33)])
+def test_overflowing_fast_row_leaves_the_slow_row(name, lens):
+    """A fast row whose own value overflows: no slow row sees it."""
+    cfg = {**MF_CONFIGS, "tiny": synth.CONFIGS["tiny"]}[name]
+    plain = synth.make_weights(cfg)
+    big = {k: (100 * v if k.endswith(".A_v") else np.full_like(v, 2.0 ** 127) if k.endswith(".B_v") else v)
+           for k, v in plain.items()}
+    pair, t, n = Pair(cfg, big, max_ctx=256, max_batch=len(lens), n_seqs=len(lens), table_seed=31), Tally(), len(lens)
+    orc = Pair(cfg, plain, max_ctx=256).orc
+    for s, m in enumerate(lens):
+        for l, (K, V) in synth.synthetic_kv(cfg, m, seq=s).items():
+            pair.kv.load(s, l, K, V)
+            pair.caches[s].load(l, K, V)
+    toks = synth.prompt_ids(cfg, n, seed=3)
+    h, z = (torch.zeros(n * w, dtype=torch.float32, device=pair.dev) for w in (cfg.d_model, cfg.vocab))
+    nxt = torch.zeros(n, dtype=torch.int32, device=pair.dev)
+    pair.model.decode_step(torch.tensor(toks, dtype=torch.int32, device=pair.dev),
+                           torch.tensor(lens, dtype=torch.int32, device=pair.dev), pair.kv.desc(), gates=[1], tau=2.0,
+                           mode="observe", next_token=nxt, h_out=h, logits=z)
+    torch.cuda.synchronize()
+    for s, m in enumerate(lens):
+        r = orc.decode_step(int(toks[s]), m, pair.caches[s], gates=[1], tau=2.0, mode="observe")
+        # a cached value on the other side of a bfloat16 rounding is 2^-8 of itself
+        t.rel(h.cpu().numpy().reshape(n, -1)[s], r.h, 2e-2, f"seq {s} h")
+        t.rel(z.cpu().numpy().reshape(n, -1)[s], r.logits, 2e-2, f"seq {s} logits")
+        t.steps += 1
+    assert t.steps == n
+
+
+@pytest.mark.parametrize("name", MF_CONFIGS)
+@pytest.mark.parametrize("n,bad", [(2, 1), (9, 6), (16, 15)])
+def test_overflowing_chunk_row_leaves_the_rows_before_it(name, n, bad):
+    """A chunk row of infinite values reaches no row before it."""
+    cfg = MF_CONFIGS[name]
+    w, ctx = synth.make_weights(cfg), 40
+    toks = [i + 1 for i in range(n)]
+    w["embed"] = w["embed"].copy()
+    w["embed"][toks[bad]] = np.inf
+    pair, t = Pair(cfg, w, max_ctx=80, table_seed=37), Tally()
+    pair.tol = max(pair.tol, 2.0 ** -7)   # (one unit in the last place of a cached value)
+    for l, (K, V) in synth.synthetic_kv(cfg, ctx).items():
+        pair.kv.load(0, l, K, V)
+        pair.caches[0].load(l, K, V)
+    pos = torch.tensor([ctx], dtype=torch.int32, device=pair.dev)
+    targets = torch.zeros(16, dtype=torch.int32, device=pair.dev)
+    pair.model.verify(torch.tensor(toks, dtype=torch.int32, device=pair.dev), n, pos, pair.kv.desc(), targets)
+    torch.cuda.synchronize()
+    ref = pair.orc.slow_chunk(toks[:bad], ctx, pair.caches[0])
+    for i in range(bad):
+        t.token(int(targets[i].item()), ref[i], pair.tol, f"row {i}")
+    pair.check_cache(0, ctx, ctx + bad, t)
+    assert t.arrays == 2 * cfg.n_layers
+    for l in range(cfg.n_layers):
+        assert not np.isfinite(pair.kv.read(0, l, ctx + bad, ctx + bad + 1)[1]).any()
