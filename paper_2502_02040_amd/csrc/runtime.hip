@@ -718,8 +718,9 @@ m2r2_status run_layers_rw(m2r2_ctx* c, const RowMap& rm, const StepIO& io, const
   const size_t lds = (size_t)kSkMinLds;
   const int nd = c->rw_nch[0], nq = c->rw_nch[1], nf = c->rw_nch[2];
   // attention: one 128-token chunk per split (two only when M2R2_ATTN_CHUNKS
-  // asks for it: measured no faster at one sequence)
-  const int S2 = c->attn_chunks == 2 ? (c->max_ctx + 2 * kSkAttnP - 1) / (2 * kSkAttnP) : 0;
+  // asks for it, within the short-chain kernel's capacity of 64 splits of 128:
+  // measured no faster at one sequence)
+  const int S2 = c->attn_chunks == 2 && c->sk_attn_S > 0 ? (c->max_ctx + 2 * kSkAttnP - 1) / (2 * kSkAttnP) : 0;
   const int SM = c->attn_chunks ? 0 : mf_splits(c, rm, kv, rm.M);
   HIP_TRY(arla_after<WB>(c, io, -1, st));   // the first interval's restart state
   for (int l = 0; l < n_layers_run; ++l) {

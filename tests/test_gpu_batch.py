@@ -240,3 +240,15 @@ def test_overflowing_chunk_row_leaves_the_rows_before_it(name, n, bad):
     assert t.arrays == 2 * cfg.n_layers
     for l in range(cfg.n_layers):
         assert not np.isfinite(pair.kv.read(0, l, ctx + bad, ctx + bad + 1)[1]).any()
+
+
+def test_attention_chunks_switch_beyond_its_capacity(monkeypatch):
+    """Two chunks per split asked for at a capacity of more splits than the
+    short-chain attention holds (64): the general attention serves it."""
+    monkeypatch.setenv("M2R2_ATTN_CHUNKS", "2")
+    monkeypatch.setenv("M2R2_ONE_LAUNCH", "0")
+    cfg = synth.CONFIGS["small_rw"]
+    pair = Pair(cfg, synth.make_weights(cfg), max_ctx=16700, table_seed=41)
+    t = Tally()
+    batch_step(pair, [16600], t)
+    assert t.steps == 1
