@@ -670,15 +670,17 @@ bool has_fast_row(const RowMap& rm) {
 // where it does not apply: a bfloat16 cache, one or two rows per sequence or
 // one sequence's chunk of slow rows.  Two workgroups are resident per compute
 // unit; about four per compute unit even out sequences of different lengths.
+// The merge holds 63 splits: where few heads and a large capacity ask for more,
+// the splits are longer (up to kMfMaxTokens each).
 int mf_splits(const m2r2_ctx* c, const RowMap& rm, const KVPtrs& kv, int rows_per_seq) {
   if (!c->D.kvbf16 || is_flops(c->cfg)) return 0;
   if (rows_per_seq > 2 && (rm.nseq > 1 || has_fast_row(rm))) return 0;
   if ((long long)kv.num_blocks * c->D.H * kv.bs >= 1LL << 31) return 0;   // rows are numbered in 32 bits
+  const int most = std::min(63, c->lay.S_max);
   const int want = std::max(1, 4 * c->cus / (rm.nseq * c->D.H));
   const int fit = (c->max_ctx + kMfMinTokens - 1) / kMfMinTokens;          // splits of at least kMfMinTokens
   const int need = (c->max_ctx + kMfMaxTokens - 1) / kMfMaxTokens;
-  const int S = std::max(need, std::min(want, fit));
-  return S <= 63 && S <= c->lay.S_max ? S : 0;
+  return need <= most ? std::max(need, std::min({want, fit, most})) : 0;
 }
 
 template <int WB, int HD>
@@ -691,8 +693,9 @@ void mf_launch(const m2r2_ctx* c, const LayerPtrs& L, const RowMap& rm, const St
 }
 
 // Attention of a pass with one or two rows: on the matrix cores where that
-// applies (SM splits), else the short-chain kernel, else (a float32 cache of
-// more than 64 splits) the general one.
+// applies (SM splits), else the short-chain kernel up to its 64 splits, else
+// the general one (a bfloat16 cache whose capacity has more: pages of 2^31
+// rows and more, or M2R2_ATTN_CHUNKS).
 template <int WB, int KB, int HD>
 void attn_launch(const m2r2_ctx* c, const LayerPtrs& L, const RowMap& rm, const StepIO& io, const KVPtrs& kv, int l,
                  int SM, hipStream_t st) {

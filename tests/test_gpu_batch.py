@@ -94,8 +94,11 @@ def test_batch_attention_context_edges(name, block_size, lens):
 def test_chunk_attention_context_edges(name, ctx, n):
     """A chunk of n slow rows after ctx cached positions: targets and the
     chunk's cache entries in every layer."""
-    cfg = MF_CONFIGS[name]
-    pair = Pair(cfg, synth.make_weights(cfg), max_ctx=ctx + 40, block_size=16, table_seed=13)
+    chunk(MF_CONFIGS[name], ctx, n, ctx + 40)
+
+
+def chunk(cfg, ctx, n, cap):
+    pair = Pair(cfg, synth.make_weights(cfg), max_ctx=cap, block_size=16, table_seed=13)
     # float32 weights with a bfloat16 cache: a value whose rounding falls on
     # the other side is one unit in the last place off, at most 2^-7 of itself
     pair.tol = max(pair.tol, 2.0 ** -7)
@@ -252,3 +255,22 @@ def test_attention_chunks_switch_beyond_its_capacity(monkeypatch):
     t = Tally()
     batch_step(pair, [16600], t)
     assert t.steps == 1
+
+
+# few heads and capacities of more than 63 splits of 128 positions
+@pytest.mark.parametrize("name", ["hd64", "hd96"])
+@pytest.mark.parametrize("cap,lens", [(8200, (8100, 60)), (16700, (16600, 8191, 1))])
+def test_batch_attention_large_capacities(name, cap, lens):
+    cfg = MF_CONFIGS[name].replace(name=f"{name}_1", n_layers=1)
+    pair = Pair(cfg, synth.make_weights(cfg), max_ctx=cap, max_batch=len(lens), n_seqs=len(lens), table_seed=43)
+    t = Tally()
+    batch_step(pair, lens, t, tol=2e-2)
+    assert t.steps == len(lens)
+
+
+@pytest.mark.parametrize("name", MF_CONFIGS)
+@pytest.mark.parametrize("ctx,cap", [(8100, 8200), (16600, 16700)])
+def test_chunk_attention_large_capacities(name, ctx, cap):
+    """16 rows behind more positions than 63 splits of the general attention
+    hold scores of (256 positions each)."""
+    chunk(MF_CONFIGS[name].replace(name=f"{name}_1", n_layers=1), ctx, 16, cap)
