@@ -1023,6 +1023,17 @@ hipError_t fattn_set_lds(int bytes) {
   return e;
 }
 
+// km_attn holds the cache rows of a split: up to kMfMaxTokens beside up to 60 KB of its own
+template <int WB>
+hipError_t mf_set_lds() {
+  const void* fns[] = {(const void*)km_attn<WB, 64, 2>,  (const void*)km_attn<WB, 96, 2>,  (const void*)km_attn<WB, 128, 2>,
+                       (const void*)km_attn<WB, 64, 16>, (const void*)km_attn<WB, 96, 16>, (const void*)km_attn<WB, 128, 16>};
+  hipError_t e = hipSuccess;
+  for (const void* f : fns)
+    if (e == hipSuccess) e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, 4 * kMfMaxTokens);
+  return e;
+}
+
 bool getenv_zero(const char* name) {
   const char* v = getenv(name);
   return v && v[0] == '0';
@@ -1803,6 +1814,7 @@ M2R2_API m2r2_status m2r2_create(const m2r2_config* cfg, const m2r2_weights* w, 
   if (e == hipSuccess) e = set_lds_limits<1, 2>(*cfg, c->resident);
   if (e == hipSuccess) e = set_lds_limits<0, 8>(*cfg, c->resident);
   if (e == hipSuccess) e = set_lds_limits<0, 16>(*cfg, c->resident);
+  if (e == hipSuccess && D.kvbf16) e = D.wbf16 ? mf_set_lds<1>() : mf_set_lds<0>();
   if (e == hipSuccess) e = sk_setup(c);
   if (e == hipSuccess) e = pk_setup(c);
   if (e == hipSuccess) {

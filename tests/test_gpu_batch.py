@@ -274,3 +274,27 @@ def test_chunk_attention_large_capacities(name, ctx, cap):
     """16 rows behind more positions than 63 splits of the general attention
     hold scores of (256 positions each)."""
     chunk(MF_CONFIGS[name].replace(name=f"{name}_1", n_layers=1), ctx, 16, cap)
+
+
+def wide(hd, heads):
+    """One layer of many heads: few splits, so a wave takes several tiles."""
+    return synth.ModelConfig(f"wide{hd}_{heads}", n_layers=1, d_model=512, n_heads=heads, head_dim=hd, ffn=512, vocab=300,
+                             rank=8, wdtype="bf16", kvdtype="bf16", seed=47)
+
+
+# (capacities at which the kernel's LDS, with the row table of a split, is above 64 KB)
+@pytest.mark.parametrize("hd,heads,cap", [(128, 32, 32768)])
+def test_batch_attention_long_splits(hd, heads, cap):
+    """Eight sequences on four splits: two to four tiles per wave, an odd
+    number of them, a masked last one after full ones."""
+    cfg, lens = wide(hd, heads), (129, 160, 257, 289, 700, 1000, 1025, 1537)
+    pair = Pair(cfg, synth.make_weights(cfg), max_ctx=cap, max_batch=8, n_seqs=8, table_seed=53)
+    t = Tally()
+    batch_step(pair, lens, t)
+    assert t.steps == 8
+
+
+@pytest.mark.parametrize("hd,heads,cap,ctx,n", [(128, 64, 40000, 4200, 16)])
+def test_chunk_attention_long_splits(hd, heads, cap, ctx, n):
+    """Chunks on 16 splits: up to three tiles per wave."""
+    chunk(wide(hd, heads), ctx, n, cap)
