@@ -168,6 +168,22 @@ struct MfWave {
       s0 = mf_mma(t.k[0][s], qh[s], s0);
       s1 = mf_mma(t.k[1][s], qh[s], s1);
     }
+    // an infinite key times a low part of q that is zero or of the other sign is
+    // NaN, the whole product infinite: such a score is its leading parts' alone
+    if (__any(__builtin_isunordered(s0[0], s0[1]) | __builtin_isunordered(s0[2], s0[3]) |
+              __builtin_isunordered(s1[0], s1[1]) | __builtin_isunordered(s1[2], s1[3]))) {
+      f32x4_t h0 = {0.f, 0.f, 0.f, 0.f}, h1 = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int s = 0; s < NS; ++s) {
+        h0 = mf_mma(t.k[0][s], qh[s], h0);
+        h1 = mf_mma(t.k[1][s], qh[s], h1);
+      }
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        s0[i] = s0[i] == s0[i] ? s0[i] : h0[i];
+        s1[i] = s1[i] == s1[i] ? s1[i] : h1[i];
+      }
+    }
     keys_done();
     float z[8], mx = -INFINITY;
 #pragma unroll

@@ -298,3 +298,63 @@ def test_batch_attention_long_splits(hd, heads, cap):
 def test_chunk_attention_long_splits(hd, heads, cap, ctx, n):
     """Chunks on 16 splits: up to three tiles per wave."""
     chunk(wide(hd, heads), ctx, n, cap)
+
+
+@pytest.mark.filterwarnings("ignore::RuntimeWarning")   # (the oracle's infinite scores)
+@pytest.mark.parametrize("name", [*MF_CONFIGS, "tiny"])
+@pytest.mark.parametrize("lens", [(5,), (200,), (700,), (5, 200, 700)])
+def test_infinite_cached_key(name, lens):
+    """One infinite element of a cached key: the position has weight zero where
+    the score is minus infinity; the other rows are not finite."""
+    cfg = {**MF_CONFIGS, "tiny": synth.CONFIGS["tiny"]}[name].replace(n_layers=1)
+    w, n = synth.make_weights(cfg), len(lens)
+    toks, seen = synth.prompt_ids(cfg, n, seed=3), 0
+    for inf in (np.inf, -np.inf):
+        pair, t = Pair(cfg, w, max_ctx=max(lens) + 20, max_batch=n, n_seqs=n, table_seed=59), Tally()
+        for s, m in enumerate(lens):
+            for l, (K, V) in synth.synthetic_kv(cfg, m, seq=s).items():
+                K = K.copy()
+                K[m // 2, 1, 7] = inf
+                pair.kv.load(s, l, K, V)
+                pair.caches[s].load(l, K, V)
+        h, p, z = (torch.zeros(n * k, dtype=torch.float32, device=pair.dev)
+                   for k in (cfg.d_model, cfg.d_model, cfg.vocab))
+        nxt = torch.zeros(n, dtype=torch.int32, device=pair.dev)
+        pair.model.decode_step(torch.tensor(toks, dtype=torch.int32, device=pair.dev),
+                               torch.tensor(lens, dtype=torch.int32, device=pair.dev), pair.kv.desc(), gates=[], tau=2.0,
+                               mode="observe", next_token=nxt, h_out=h, p_out=p, logits=z)
+        torch.cuda.synchronize()
+        for s, m in enumerate(lens):
+            r = pair.orc.decode_step(int(toks[s]), m, pair.caches[s], gates=[], tau=2.0, mode="observe")
+            for got, ref, what in ((h, r.h, "h"), (p, r.p, "p"), (z, r.logits, "logits")):
+                got = got.cpu().numpy().reshape(n, -1)[s]
+                if np.isfinite(ref).all():
+                    t.rel(got, ref, 2e-2, f"seq {s} {what}")   # (a rounding of a cached value)
+                    seen += 1
+                else:
+                    assert not np.isfinite(got).any(), f"seq {s} {what}"
+    assert seen >= 2 * n   # (a slow row's h and logits with one of the signs)
+
+
+@pytest.mark.filterwarnings("ignore::RuntimeWarning")
+@pytest.mark.parametrize("name", MF_CONFIGS)
+@pytest.mark.parametrize("ctx", [5, 700])
+def test_infinite_cached_key_chunk(name, ctx):
+    """The same for the rows of a chunk (one layer: a row that is not finite reaches no other)."""
+    cfg = MF_CONFIGS[name].replace(n_layers=1)
+    pair, t, n = Pair(cfg, synth.make_weights(cfg), max_ctx=ctx + 20, table_seed=61), Tally(), 16
+    for l, (K, V) in synth.synthetic_kv(cfg, ctx).items():
+        K = K.copy()
+        K[ctx // 2, 1, 7] = np.inf
+        pair.kv.load(0, l, K, V)
+        pair.caches[0].load(l, K, V)
+    toks = [int(x) for x in synth.prompt_ids(cfg, n, seed=9)]
+    pos = torch.tensor([ctx], dtype=torch.int32, device=pair.dev)
+    targets = torch.zeros(16, dtype=torch.int32, device=pair.dev)
+    pair.model.verify(torch.tensor(toks, dtype=torch.int32, device=pair.dev), n, pos, pair.kv.desc(), targets)
+    torch.cuda.synchronize()
+    ref = pair.orc.slow_chunk(toks, ctx, pair.caches[0])
+    finite = [i for i in range(n) if np.isfinite(ref[i]).all()]
+    for i in finite:
+        t.token(int(targets[i].item()), ref[i], pair.tol, f"row {i}")
+    assert 0 < len(finite) < n and t.compared > 0
