@@ -921,8 +921,11 @@ __global__ __launch_bounds__(kTpThreads, 2) void kt_head(Dims D, const void* lm_
         const int i2 = __shfl_xor(idx, o);
         if (z2 > z || (z2 == z && i2 < idx)) { z = z2; idx = i2; }
       }
-      // (the same thread for the same slot in every group; ids rise from group to group)
-      if (live && n == 0 && z > bz_s[t * kMaxRows + k]) {
+      // (the same thread for the same slot in every group; ids rise from group
+      // to group, so a tie takes a new id only over the empty slot's: a row of
+      // infinitely low logits has the lowest id, too)
+      const float bz = bz_s[t * kMaxRows + k];
+      if (live && n == 0 && (z > bz || (z == bz && idx < bi_s[t * kMaxRows + k]))) {
         bz_s[t * kMaxRows + k] = z;
         bi_s[t * kMaxRows + k] = idx;
       }

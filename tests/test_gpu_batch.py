@@ -358,3 +358,23 @@ def test_infinite_cached_key_chunk(name, ctx):
     for i in finite:
         t.token(int(targets[i].item()), ref[i], pair.tol, f"row {i}")
     assert 0 < len(finite) < n and t.compared > 0
+
+
+@pytest.mark.parametrize("n", [3, 8, 9, 16])
+def test_head_of_infinitely_low_logits(n):
+    """Every logit overflows to minus infinity: the arg-max is the lowest id."""
+    cfg = synth.CONFIGS["small_bf16"].replace(n_layers=1)
+    w = {k: v.copy() for k, v in synth.make_weights(cfg).items()}
+    for k in w:
+        if k.endswith(".wo") or k.endswith(".wd"):
+            w[k][:] = 0   # the head's input is the embedding
+    w["embed"][:, 0], w["lm_head"][:, 0] = 1, -(2.0 ** 127)
+    w["final_norm"][:] = 0
+    w["final_norm"][0] = 16
+    pair = Pair(cfg, w, max_ctx=32)
+    pos = torch.zeros(1, dtype=torch.int32, device=pair.dev)
+    targets = torch.full((16,), -1, dtype=torch.int32, device=pair.dev)
+    toks = [int(x) for x in synth.prompt_ids(cfg, n, seed=9)]
+    pair.model.verify(torch.tensor(toks, dtype=torch.int32, device=pair.dev), n, pos, pair.kv.desc(), targets)
+    torch.cuda.synchronize()
+    assert targets[:n].tolist() == [0] * n
