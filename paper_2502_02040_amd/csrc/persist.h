@@ -665,8 +665,9 @@ __device__ __forceinline__ void pk_phase_att(int l, uint32_t& target, PkShared& 
       constexpr int WESZ = WB ? 2 : 4;
       PkAttLds<HD, WB>& A = *(PkAttLds<HD, WB>*)pk_dyn;
       // small models: a short context is one workgroup's, and a single split
-      // merges nothing (tiny float32 decoder at 16 positions: 78.4 -> 69.2 us per
-      // step; on 6 KB rows the second path costs every context 0.4 %)
+      // merges nothing (us per step at 64 positions, one split, against 65, all
+      // of them: float32 decoder of d 256 67.8, 76.9; bfloat16 of d 512 92.2,
+      // 114.7; on 6 KB rows the second path costs every context 0.4 %)
       constexpr bool ONE = ND <= 2;
       const int H = D.H;
       const int S = ONE && ctx <= kPkOneSplit ? 1 : P.S;

@@ -1174,12 +1174,20 @@ hipError_t pk_setup(m2r2_ctx* c) {
   if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
   if (e != hipSuccess) return e;
   if (D.r % 4 || 2 + 2 * D.r > 64 || cus < 1 || cus > kPkMaxWG || D.H > cus) return hipSuccess;
-  // a model whose largest phase is small takes 64 workgroups: the grid barrier
-  // and the sums over the workgroups' slots cost less than the bytes (tiny
-  // float32 decoder, 2 MB phases: 81.4 us per step on 256, 76.9 on 64, 80.4 on 32)
-  const size_t wsz = D.wbf16 ? 2 : 4;
-  const size_t phase = wsz * D.d * std::max({3 * D.qdim, 2 * D.F, D.V});
-  const int grid = phase <= ((size_t)8 << 20) ? std::max(D.H, std::min(cus, 64)) : cus;
+  // 64 workgroups instead of one per compute unit where the grid barrier, the
+  // sums over the workgroups' slots and the merge of half as many splits cost
+  // less than the bytes: small phases, and contexts of more than the one split
+  // that either grid gives short ones, up to where a split is long.  Float32
+  // decoder of d 256, us per step on 64 against 256 workgroups (context 16 / 1000 / 8000):
+  //   largest phase 2 MB       66.4, 65.5 / 76.9, 82.8 / 89.8, 85.1
+  //   (vocabulary 2048)        68.8, 65.1 / 79.1, 82.4
+  //   4 MB                     70.7, 65.7 / 80.3, 82.5 / 92.0, 84.7
+  //   8 MB                     74.2, 66.0 / 83.8, 83.2 / 96.2, 85.6
+  // and at 4000 positions 77.6, 82.9 (2 MB).  The bfloat16 decoder of d 512 (2 MB)
+  // gains less than it loses: 99.1, 90.2 / 113.3, 115.3 / 128.1, 125.6.
+  const size_t phase = (size_t)4 * D.d * std::max({3 * D.qdim, 2 * D.F, D.V});
+  const bool small = !D.wbf16 && phase <= ((size_t)2 << 20) && c->max_ctx > kPkOneSplit && c->max_ctx <= 4096;
+  const int grid = small ? std::max(D.H, std::min(cus, 64)) : cus;
   const int S = std::min(kPkMaxSplits, std::max(1, grid / D.H));
   if (S > c->lay.S_max) return hipSuccess;
   const int nd = c->rw_nch[0], nq = c->rw_nch[1], nf = c->rw_nch[2];

@@ -122,6 +122,8 @@ def chunk(cfg, ctx, n, cap):
 @pytest.mark.parametrize("name,ctx,cap", [
     # one split up to 64 positions, then one per head's share of the workgroups; 256 positions per pass
     *[("tiny", n, 300) for n in (0, 1, 63, 64, 65, 257)],
+    # float32 on one workgroup per compute unit: capacities of one split, and above 4096
+    *[("tiny", n, 64) for n in (0, 63)], *[("tiny", n, 4200) for n in (10, 65, 4100)],
     *[("small_rw", n, 300) for n in (0, 31, 64, 65, 257)],
     ("small_rw", 1025, 2048),
     # more than 63 splits of 128 positions; more than 1024 positions per split
