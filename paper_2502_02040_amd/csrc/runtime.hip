@@ -785,11 +785,15 @@ bool tp_pass(const m2r2_ctx* c, const RowMap& rm) { return c->ws.XB && rm.M > 2;
 // Fast rows of such a pass: none, or those of a dual batch (row 2k + 1 of every pair).
 int fast_rows(const RowMap& rm) { return has_fast_row(rm) ? rm.M / 2 : 0; }
 
-// A wave's share of a reduction of length K, in steps: the instantiation (0: streamed).
+// A wave's share of a reduction of length K, in steps: the instantiation (0:
+// streamed).  An instantiation requests all its steps, also those past the
+// share: 4 steps (d 1024) on that of 12 made a layer of eight dual sequences
+// 59.9 us, 49.8 on that of 4 (d 768: 53.7, 42.9; the per-tile kernels 52.9, 50.6).
 #define M2R2_TP_LAUNCH(NAME, K, T, ...)                                                            \
   do {                                                                                             \
     const int per_ = ((K) / 32 + kTpWaves - 1) / kTpWaves;                                         \
     if (per_ <= 2) NAME<2, MT><<<c->cus, kTpThreads, tp_lds_bytes(T), st>>>(__VA_ARGS__);           \
+    else if (per_ <= 4) NAME<4, MT><<<c->cus, kTpThreads, tp_lds_bytes(T), st>>>(__VA_ARGS__);      \
     else if (per_ <= 12) NAME<12, MT><<<c->cus, kTpThreads, tp_lds_bytes(T), st>>>(__VA_ARGS__);    \
     else NAME<0, MT><<<c->cus, kTpThreads, tp_lds_bytes(T), st>>>(__VA_ARGS__);                     \
   } while (0)

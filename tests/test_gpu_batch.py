@@ -380,3 +380,15 @@ def test_head_of_infinitely_low_logits(n):
     pair.model.verify(torch.tensor(toks, dtype=torch.int32, device=pair.dev), n, pos, pair.kv.desc(), targets)
     torch.cuda.synchronize()
     assert targets[:n].tolist() == [0] * n
+
+
+@pytest.mark.parametrize("d", [512, 544, 768, 1024, 1056, 1536])
+@pytest.mark.parametrize("B", [3, 8])
+def test_reduction_lengths(d, B):
+    """Projections whose waves have 2, 3, 4, 5 and 6 steps of the reduction,
+    whole and ragged: the edges of the resident instantiations."""
+    cfg = synth.CONFIGS["small_bf16"].replace(name=f"d{d}", d_model=d, ffn=d, n_layers=2)
+    pair = Pair(cfg, synth.make_weights(cfg), max_ctx=80, max_batch=B, n_seqs=B, table_seed=67)
+    t = Tally()
+    batch_step(pair, [3, 40, 17, 0, 65, 33, 9, 21][:B], t)
+    assert t.steps == B
