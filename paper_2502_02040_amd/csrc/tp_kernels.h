@@ -945,7 +945,7 @@ __global__ __launch_bounds__(kTpThreads, 2) void kt_head(Dims D, const void* lm_
     st_agent(&ws.lm_idx[(size_t)blockIdx.x * kMaxRows + threadIdx.x], idx);
   }
   if (!arrive_last(ws.lm_cnt, wgs, &last_flag)) return;
-  head_finish(D, rm, rml, ws, io, kv, wgs, nh, ssum, false);
+  head_finish<4>(D, rm, rml, ws, io, kv, wgs, nh, ssum, false);
 }
 
 }  // namespace m2r2
