@@ -26,6 +26,8 @@
 // last one also forms the rows' own keys and values, writes them to the cache
 // and adds their terms; the last to arrive merges the partials.
 #pragma once
+#include <type_traits>
+
 #include "step_kernels.h"
 
 namespace m2r2 {
@@ -144,12 +146,13 @@ struct MfWave {
   }
 
   // see(t): whether the lane's query sees token t of the tile; keys_done()
-  // runs once the tile's keys are no longer needed
-  template <class See>
+  // runs once the tile's keys are no longer needed.  FIX: infinite keys are
+  // looked for; without, they may leave NaN in l_run
+  template <bool FIX, class See>
   __device__ __forceinline__ void tile(const Tile& t, float scale, See see) {
-    tile(t, scale, see, [] {});
+    tile<FIX>(t, scale, see, [] {});
   }
-  template <class See, class Done>
+  template <bool FIX, class See, class Done>
   __device__ __forceinline__ void tile(const Tile& t, float scale, See see, Done keys_done) {
     const int g = (threadIdx.x & 63) >> 4;
     f32x4_t s0 = {0.f, 0.f, 0.f, 0.f}, s1 = {0.f, 0.f, 0.f, 0.f};
@@ -170,8 +173,8 @@ struct MfWave {
     }
     // an infinite key times a low part of q that is zero or of the other sign is
     // NaN, the whole product infinite: such a score is its leading parts' alone
-    if (__any(__builtin_isunordered(s0[0], s0[1]) | __builtin_isunordered(s0[2], s0[3]) |
-              __builtin_isunordered(s1[0], s1[1]) | __builtin_isunordered(s1[2], s1[3]))) {
+    if (FIX && __any(__builtin_isunordered(s0[0], s0[1]) | __builtin_isunordered(s0[2], s0[3]) |
+                     __builtin_isunordered(s1[0], s1[1]) | __builtin_isunordered(s1[2], s1[3]))) {
       f32x4_t h0 = {0.f, 0.f, 0.f, 0.f}, h1 = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
       for (int s = 0; s < NS; ++s) {
@@ -497,14 +500,15 @@ __global__ __launch_bounds__(kMfThreads, 2) void km_attn(Dims D, LayerPtrs L, Ro
   mw_.init(q_s[q], true);   // (rows beyond the sequence's are zero)
   while (tt < ntile) {
     if (tt + kMfWaves < ntile) MW::load(trow + (tt + kMfWaves) * kMfTile, kb, vb, tb);
-    mw_.tile(ta, scale, [left = nt - tt * kMfTile](int t) { return t < left; });
+    mw_.template tile<false>(ta, scale, [left = nt - tt * kMfTile](int t) { return t < left; });
     tt += kMfWaves;
     if (tt >= ntile) break;
     if (tt + kMfWaves < ntile) MW::load(trow + (tt + kMfWaves) * kMfTile, kb, vb, ta);
-    mw_.tile(tb, scale, [left = nt - tt * kMfTile](int t) { return t < left; });
+    mw_.template tile<false>(tb, scale, [left = nt - tt * kMfTile](int t) { return t < left; });
     tt += kMfWaves;
   }
-  if (own && wv == (ntile & (kMfWaves - 1))) {
+  const bool own_wave = own && wv == (ntile & (kMfWaves - 1));
+  auto own_tile = [&](auto fix) {
     // the rows' own keys: a slow row sees the slow rows up to itself, as cached
 #pragma unroll
     for (int s = 0; s < NS; ++s) {
@@ -525,7 +529,18 @@ __global__ __launch_bounds__(kMfThreads, 2) void km_attn(Dims D, LayerPtrs L, Ro
       ta.v[4 + t] = u32x4_t{0u, 0u, 0u, 0u};
     }
     const bool slow = q < R && q != fast_i;
-    mw_.tile(ta, scale, [&](int t) { return slow && t <= q && t != fast_i; });
+    mw_.template tile<decltype(fix)::value>(ta, scale, [&](int t) { return slow && t <= q && t != fast_i; });
+  };
+  if (own_wave) own_tile(std::false_type{});
+  // A NaN score (an infinite key, perhaps): once more, with such keys looked
+  // for (in the loop above that costs eight sequences of 4096 positions 1.6 us a layer)
+  if (__any(mw_.l_run != mw_.l_run)) {
+    mw_.init(q_s[q], true);
+    for (tt = wv; tt < ntile; tt += kMfWaves) {
+      MW::load(trow + tt * kMfTile, kb, vb, ta);
+      mw_.template tile<true>(ta, scale, [left = nt - tt * kMfTile](int t) { return t < left; });
+    }
+    if (own_wave) own_tile(std::true_type{});
   }
   // ---- the waves' results, combined --------------------------------------------
   mw_.store(q < R, &m_s[wv][q], &l_s[wv][q], acc_s[wv][min(q, RMAX - 1)]);

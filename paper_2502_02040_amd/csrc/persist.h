@@ -893,7 +893,7 @@ __device__ __forceinline__ void pk_phase_att(int l, uint32_t& target, PkShared& 
             for (int t = wv * kMfTile; t < n; t += STEP) {
               const uint32_t* nt = A.trow + t + STEP;
               const bool more = t + STEP < n;
-              w.tile(ta, scale, [left = n - t](int x) { return x < left; }, [&] { if (more) MW::load_k(nt, kb, ta); });
+              w.template tile<true>(ta, scale, [left = n - t](int x) { return x < left; }, [&] { if (more) MW::load_k(nt, kb, ta); });
               if (more) MW::load_v(nt, vb, ta);
             }
           }
