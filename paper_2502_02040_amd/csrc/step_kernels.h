@@ -1048,7 +1048,7 @@ __global__ __launch_bounds__(kEmbedThreads) void k_embed(Dims D, const void* emb
     bin_d_at(ws, 0, b, m)[c] = (b == 0 && c < 3) ? ss : 0.f;
   }
   if (init_ctl && m == 0) {
-    for (int s = threadIdx.x; s < kMaxSeq; s += 256) {
+    for (int s = threadIdx.x; s < kMaxSeq; s += kEmbedThreads) {
       ws.exited[s] = 0;
       ws.exitb[s] = D.n_layers;
     }
