@@ -285,7 +285,7 @@ def wide(hd, heads):
 
 
 # (capacities at which the kernel's LDS, with the row table of a split, is above 64 KB)
-@pytest.mark.parametrize("hd,heads,cap", [(128, 32, 32768)])
+@pytest.mark.parametrize("hd,heads,cap", [(64, 32, 2048), (96, 32, 2048), (128, 32, 32768)])
 def test_batch_attention_long_splits(hd, heads, cap):
     """Eight sequences on four splits: two to four tiles per wave, an odd
     number of them, a masked last one after full ones."""
@@ -296,7 +296,8 @@ def test_batch_attention_long_splits(hd, heads, cap):
     assert t.steps == 8
 
 
-@pytest.mark.parametrize("hd,heads,cap,ctx,n", [(128, 64, 40000, 4200, 16)])
+@pytest.mark.parametrize("hd,heads,cap,ctx,n", [(64, 64, 3000, 2600, 5), (96, 64, 5000, 4200, 9),
+                                                (128, 64, 40000, 4200, 16)])
 def test_chunk_attention_long_splits(hd, heads, cap, ctx, n):
     """Chunks on 16 splits: up to three tiles per wave."""
     chunk(wide(hd, heads), ctx, n, cap)
@@ -392,3 +393,23 @@ def test_reduction_lengths(d, B):
     t = Tally()
     batch_step(pair, [3, 40, 17, 0, 65, 33, 9, 21][:B], t)
     assert t.steps == B
+
+
+# q/k/v of 3072 rows per matrix, o and down of 3072 rows, on 256 compute units: tiles of 12 rows
+TILE12 = {"qkv": wide(96, 32).replace(name="qkv12"), "o_down": wide(128, 4).replace(name="o_down12", d_model=3072)}
+
+
+@pytest.mark.parametrize("name", TILE12)
+@pytest.mark.parametrize("B", [2, 3, 8])
+def test_batch_on_tiles_of_12_rows(name, B):
+    cfg = TILE12[name]
+    pair = Pair(cfg, synth.make_weights(cfg), max_ctx=80, max_batch=B, n_seqs=B, table_seed=71)
+    t = Tally()
+    batch_step(pair, [3, 40, 17, 0, 65, 33, 9, 21][:B], t)
+    assert t.steps == B
+
+
+@pytest.mark.parametrize("name", TILE12)
+@pytest.mark.parametrize("n", [3, 16])
+def test_chunk_on_tiles_of_12_rows(name, n):
+    chunk(TILE12[name], 40, n, 80)

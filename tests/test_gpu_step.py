@@ -314,14 +314,26 @@ def test_draft_and_verify(name, gamma, exit_layer):
     assert t.compared >= 4 * (gamma + 1)
 
 
+@pytest.mark.parametrize("name", ["tiny", "small_rw", "hd64"])
+def test_plain_steps_and_drafts_on_the_multi_kernel_path(name, monkeypatch):
+    """One row (the slow row alone, the fast row alone) outside the one-launch
+    step; hd64: float32 weights with a bfloat16 cache."""
+    monkeypatch.setenv("M2R2_ONE_LAUNCH", "0")
+    monkeypatch.setitem(synth.CONFIGS, "hd64", synth.CONFIGS["tiny"].replace(name="hd64", kvdtype="bf16"))
+    monkeypatch.setattr("tests.gpu_harness.tol_of", lambda cfg: 2e-2 if cfg.kvdtype == "bf16" else 1e-4)
+    test_single_stream_step(name)
+    test_draft_and_verify(name, 3, 2)
+
+
 @pytest.mark.parametrize("name", CASES)
-@pytest.mark.parametrize("chunks,B", [("1", 3), ("2", 3), ("4", 3), ("1", 8)])
+@pytest.mark.parametrize("chunks,B", [("1", 3), ("2", 3), ("4", 3), ("1", 8), ("0", 3), ("0", 8)])
 def test_batched_dual_step(name, chunks, B, monkeypatch):
     """Three (eight) sequences with different context lengths decoded
-    together (two rows each: the batched short-chain attention with one, two
-    or four 128-token chunks per split, and the 8-row (16-row) tile GEMVs):
-    every sequence's logits, h, p, signal, token and cache entry match the
-    oracle step by step."""
+    together (two rows each) over several advancing steps: every sequence's
+    logits, h, p, signal, token and cache entry match the oracle step by step.
+    0 chunks: the attention that the sizes choose (the matrix cores for a
+    bfloat16 cache); else the batched short-chain attention with one, two or
+    four 128-token chunks per split."""
     monkeypatch.setenv("M2R2_ATTN_CHUNKS", chunks)
     cfg = synth.CONFIGS[name]
     w = synth.make_weights(cfg)
