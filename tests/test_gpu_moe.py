@@ -145,6 +145,23 @@ def test_moe_dual_step_observe(name, slots):
     assert t.steps >= 6 and t.compared >= 6 * t.steps
 
 
+@pytest.mark.parametrize("name", ["small_moe", "small_moe_rw"])
+def test_moe_capacity_above_64_splits(name, monkeypatch):
+    """8100 cached positions at a capacity of more splits of 128 than the
+    short-chain attention has."""
+    pair = MoePair(name, slots=5, max_ctx=8300)
+
+    def load(prompt, t):
+        for l, (K, V) in synth.synthetic_kv(pair.cfg, len(prompt)).items():
+            pair.kv.load(0, l, K, V)
+            pair.cache.load(l, K, V)
+        return prompt[-1]
+
+    monkeypatch.setattr(pair, "prefill", load)
+    t, *_ = pair.run(2, prompt_len=8100)
+    assert t.steps >= 1
+
+
 @pytest.mark.parametrize("name", ["small_moe_f32", "small_moe_rw"])
 @pytest.mark.parametrize("resident", [False, True])
 def test_moe_exit_mode_fills_skipped_layers(name, resident):
