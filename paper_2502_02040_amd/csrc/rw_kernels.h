@@ -869,11 +869,8 @@ __global__ __launch_bounds__(kRwThreads) void kr_head(Dims D, const void* lm_hea
     }
   } epi{&D, hrow, inv_rms, io.logits_out, 0, {-INFINITY, -INFINITY}, {0x7fffffff, 0x7fffffff}};
   typename Epi::Ops ops[decltype(st)::P];
-  HeadStates hs;
-  hs.load(D, rm, ws, io, gridDim.x);
   __builtin_amdgcn_sched_barrier(0);
   st.begin(row_ptr, u0, u1, epi, ops);
-  hs.store(D, rm, ws, io);
   __builtin_amdgcn_sched_barrier(0);
   if (tid < rm.nseq) ex_in[tid] = exv;
   sk_rm_copy(rmu, rm);
@@ -902,6 +899,9 @@ __global__ __launch_bounds__(kRwThreads) void kr_head(Dims D, const void* lm_hea
   rw_store_pieces<true>(xp, D.d, actf);
   epi.nh = nh;
   st.run(row_ptr, u0, u1, actf, D.d, epi, ops);
+  HeadStates hs;
+  hs.load(D, rm, ws, io, gridDim.x);
+  hs.store(D, rm, ws, io);
   if (lowrank) {
     // logits z_v = head_b[v] . lrz for this wave's rows, one row per lane
     const int hr = D.hr;

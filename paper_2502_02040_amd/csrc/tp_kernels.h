@@ -877,12 +877,12 @@ __global__ __launch_bounds__(kTpThreads, 2) void kt_head(Dims D, const void* lm_
   }
   const int exv = ws.exited[min((int)threadIdx.x, rm.nseq - 1)];
   const int wgs = min((int)gridDim.x, n_tiles);
+  __builtin_amdgcn_sched_barrier(0);
+  tc.begin(n_local, ptr);
   HeadStates hs;
   hs.load(D, rm, ws, io, wgs);
   __builtin_amdgcn_sched_barrier(0);
-  tc.begin(n_local, ptr);
   sk_rm_copy(rmu, rm);
-  hs.store(D, rm, ws, io);
   if (threadIdx.x < T * kMaxRows) {
     bz_s[threadIdx.x] = -INFINITY;
     bi_s[threadIdx.x] = 0x7fffffff;
@@ -931,6 +931,7 @@ __global__ __launch_bounds__(kTpThreads, 2) void kt_head(Dims D, const void* lm_
       }
     }
   });
+  hs.store(D, rm, ws, io);
   __syncthreads();
   if (threadIdx.x < nh) {
     float z = -INFINITY;
