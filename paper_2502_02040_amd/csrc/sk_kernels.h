@@ -365,12 +365,13 @@ __device__ __forceinline__ void sk_finish(const SkPlan& p, const SkWS& sk, int g
   }
 }
 
-// sum_{j<r} B[row][j] u[j] for an adapter up-factor B [rows][r] (r <= 32,
-// r a multiple of 8 (bf16) or 4 (f32)): every load issued before use.
+// sum_{j<r} B[row][j] u[j] for an adapter up-factor B [rows][r] (r <= 32): where
+// r is a multiple of 8 (bf16) or 4 (f32), every load is issued before use.
 template <int WB>
 __device__ __forceinline__ float sk_dot_b(const void* B, int row, int r, const float* u) {
   constexpr int EPC = WB ? 8 : 4;                 // elements per 16-byte chunk
   constexpr int NC = kMaxRank / EPC;
+  if (r % EPC) return dot_row_t<WB>(B, row, r, u);   // rows of no whole chunks (uniform)
   const int nc = r / EPC;
   const u32x4_t* p = (const u32x4_t*)((const char*)B + (size_t)row * r * (WB ? 2 : 4));
   u32x4_t c[NC];

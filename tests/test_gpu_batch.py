@@ -413,3 +413,16 @@ def test_batch_on_tiles_of_12_rows(name, B):
 @pytest.mark.parametrize("n", [3, 16])
 def test_chunk_on_tiles_of_12_rows(name, n):
     chunk(TILE12[name], 40, n, 80)
+
+
+@pytest.mark.parametrize("rank,ctx", [(8, 0), (8, 33), (8, 200), (4, 33), (12, 33)])
+@pytest.mark.parametrize("wdtype,kvdtype", [("bf16", "bf16"), ("bf16", "f32"), ("f32", "f32")])
+def test_one_sequence_on_the_stream_k_projections(rank, ctx, wdtype, kvdtype):
+    """Rows that are no whole 1 KB pieces, at least eight blocks each; ranks
+    whose adapter rows are no whole 16 bytes."""
+    cfg = synth.CONFIGS["small_bf16"].replace(name=f"streamk{rank}", d_model=544, n_heads=3, ffn=608, rank=rank,
+                                              wdtype=wdtype, kvdtype=kvdtype)
+    pair = Pair(cfg, synth.make_weights(cfg), max_ctx=256, table_seed=73)
+    t = Tally()
+    batch_step(pair, [ctx], t, tol=2e-2 if kvdtype == "bf16" else 1e-3)
+    assert t.steps == 1
