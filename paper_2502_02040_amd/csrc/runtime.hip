@@ -418,11 +418,11 @@ struct m2r2_ctx {
   // stream-K GEMVs of the one- and two-row class
   bool sk_on = false;
   int sk_grid = 0;
-  int sk_attn_S = 0;   // splits of the stream-K path's attention (0: the general attention kernel)
+  int sk_attn_S = 0;   // splits of the short-chain attention (0: more than it holds)
   bool rw_on = false;  // row-per-wave GEMVs for the one- and two-row class
   int rw_nch[3] = {0, 0, 0};   // 1 KB pieces per row for reductions over d, qdim, ffn
   int rw_nw[2] = {8, 8};       // waves per workgroup of the o and down projections
-  int attn_chunks = 0;         // batched short-chain attention: 128-token chunks per split (0: by size)
+  int attn_chunks = 0;         // short-chain attention with this many 128-token chunks per split (0: what the sizes choose)
   // one-launch decode step (one sequence, one or two rows): instantiation,
   // grid (one workgroup per compute unit), attention splits per head, LDS
   struct {
@@ -711,7 +711,7 @@ void attn_launch(const m2r2_ctx* c, const LayerPtrs& L, const RowMap& rm, const 
   }
 }
 
-// One or two rows: row-per-wave GEMVs and the short-chain attention.
+// One or two rows: row-per-wave GEMVs and the attention of attn_launch.
 template <int WB, int KB, int HD>
 m2r2_status run_layers_rw(m2r2_ctx* c, const RowMap& rm, const StepIO& io, const KVPtrs& kv, int n_layers_run,
                           hipStream_t st) {
@@ -848,8 +848,9 @@ m2r2_status run_layers_t(m2r2_ctx* c, const RowMap& rm, const StepIO& io, const 
   const int nqkv = 3 * D.qdim + 3 * D.r;
   int rows_per_seq = 1;
   for (int s = 0; s < rm.nseq; ++s) rows_per_seq = std::max(rows_per_seq, (int)rm.cnt[s]);
-  // one or two rows per sequence (batched decoding): the short-chain
-  // attention with fixed splits; longer chunks: the general kernel
+  // attention: on the matrix cores where that applies (SM below); else one or
+  // two rows per sequence (batched decoding) take the short-chain kernel with
+  // fixed splits, longer chunks the general one
   const bool short_attn = c->sk_attn_S > 0 && rows_per_seq <= 2;
   // many splits in flight (batched long contexts): two 128-token chunks per
   // split, the second chunk's loads overlapping the first chunk's work
@@ -1070,7 +1071,7 @@ hipError_t sk_setup(m2r2_ctx* c) {
   c->sk_on = false;
   const m2r2_config& cf = c->cfg;
   // a mixture-of-experts model uses the row-per-wave q/k/v and o projections,
-  // the short-chain attention and the row-per-wave head (its MLP has kernels
+  // the attention of attn_launch and the row-per-wave head (its MLP has kernels
   // of its own); the stream-K GEMVs, whose partial slots its layout does not
   // hold, stay off
   const bool moe = is_moe(cf);
